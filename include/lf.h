@@ -321,12 +321,12 @@ typedef struct {
  * bounded_prefetch: 4 (default), 8 or 16 -- pixel metadata steps in flight
  * per wave in the bounded SGM with 64 lanes per line (their costs run half as
  * many steps ahead); bounded_lanes: 16, 32 or 64 (default) -- lanes per path line
- * of the bounded SGM (the wavefront-to-path schedule: 64/bounded_lanes lines per
- * wave, a line's range covered in chunks of that many hypotheses);
- * bounded_offsets: 32 (default) or 64 -- the bounded SGM with 64 lanes per line
- * addresses its volumes with 32-bit offsets where their worst-case size is below
- * 2^31 bytes and with 64-bit addresses otherwise; 64 takes the 64-bit form
- * everywhere (the form of very large volumes, selectable for testing). */
+ * of the bounded SGM (the wavefront-to-path schedule): 64 takes one line per wave
+ * where the lines are few and four where they are many, 16 and 32 four everywhere;
+ * bounded_offsets: 32 (default) or 64 -- the bounded SGM addresses its volumes with
+ * 32-bit offsets where their worst-case size is below 2^31 bytes, and with 64-bit
+ * addresses and one line per wave otherwise; 64 takes that form everywhere (the
+ * form of very large volumes, selectable for testing). */
 typedef struct {
     int32_t cost_cells_per_thread;
     int32_t cost_stride;

@@ -230,7 +230,7 @@ lf_status lf_plan_autotune(lf_plan* p, hipStream_t stream, int32_t reps, lf_tuni
     };
     // Phase 1: candidate i takes the i-th value of every list; the stages are
     // timed separately, so each stage's parameter is chosen on its own.
-    const int cpt[3] = {2, 4, 8}, dd[3] = {4, 8, 16}, bl[3] = {16, 32, 64};
+    const int cpt[3] = {2, 4, 8}, dd[3] = {4, 8, 16}, bl[3] = {16, 64, 64};
     double best_cost = 1e30, best_dense = 1e30, best_bounded = 1e30;
     lf::Tuning best = p->tune;
     best.cost_stride = 1;

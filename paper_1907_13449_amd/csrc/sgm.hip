@@ -29,6 +29,7 @@
 #include <algorithm>
 #include <climits>
 #include <type_traits>
+#include <utility>
 
 namespace lf {
 namespace {
@@ -53,9 +54,35 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
 
 // Path directions (du, dv): the 8 axis and diagonal neighbours, then the 8
 // knight moves of the 16-path setting (Sec. 4.3).
-const int kDirs[16][2] = {{1, 0},  {-1, 0},  {0, 1},  {0, -1}, {1, 1},  {-1, -1},
-                          {1, -1}, {-1, 1},  {1, 2},  {-1, -2}, {2, 1},  {-2, -1},
-                          {2, -1}, {-2, 1},  {1, -2}, {-1, 2}};
+constexpr int kDirs[16][2] = {{1, 0},  {-1, 0},  {0, 1},  {0, -1}, {1, 1},  {-1, -1},
+                              {1, -1}, {-1, 1},  {1, 2},  {-1, -2}, {2, 1},  {-2, -1},
+                              {2, -1}, {-2, 1},  {1, -2}, {-1, 2}};
+
+// kDirs[r][c] + 2 of every direction, four bits each: a wave-uniform r reads its
+// direction by a scalar shift.
+constexpr uint64_t packed_dirs(int c) {
+    uint64_t x = 0;
+    for (int r = 0; r < 16; ++r) x |= (uint64_t)(kDirs[r][c] + 2) << (4 * r);
+    return x;
+}
+__host__ __device__ inline int dir_u(int r) {
+    constexpr uint64_t x = packed_dirs(0);
+    return (int)(x >> (4 * r) & 15) - 2;
+}
+__host__ __device__ inline int dir_v(int r) {
+    constexpr uint64_t x = packed_dirs(1);
+    return (int)(x >> (4 * r) & 15) - 2;
+}
+
+// f(integral_constant 0), ..., f(integral_constant n - 1)
+template <int n, class F, int... I>
+__device__ __forceinline__ void static_for_(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int n, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    static_for_<n>(f, std::make_integer_sequence<int, n>());
+}
 constexpr int kMaxPaths = 16;
 
 // A path starts at every pixel whose predecessor p - r lies outside the image:
@@ -951,140 +978,523 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void sgm_bounded_paths_kernel(
     }
 }
 
-// The bounded SGM with G lanes per path line (G = 16 or 32: 64/G lines per wave).
-// Most pixels keep a window of 2*lambda+1 hypotheses, so one wave per line
-// leaves most lanes idle; here a line's G lanes cover its pixel's range in
-// chunks of G hypotheses (one chunk for a narrow window, ceil(N/G) for a
-// full-range pixel), lane j of chunk c holding k = lo + G*c + j.
+// The bounded SGM with 16 lanes (one DPP row) per path line, four lines per wave.
 //
-// A pixel's range need not overlap its predecessor's, so the previous path costs
-// are kept by hypothesis index, not by lane: each line has two LDS rows of N + 2
-// entries (k = -1 .. N), written on alternate steps.  An entry holds the path
-// cost in its low 16 bits and the step that wrote it in the high 16 bits; at
-// step s the predecessor's entries are those tagged s - 1, and subtracting
-// (s-1) << 16 leaves their value while every other entry (older steps, never
-// written) becomes >= 65536, which loses to m + P2 <= 65535 and does not wrap
-// when P1 is added (path costs <= cap + P2 <= 65535 - P2).  So the terms of
-// Eq. (8) outside R(p - r) are omitted without clearing anything.  m, the
-// minimum over R(p - r), is the row minimum of the previous step's costs.
-constexpr int kB16Waves = 4;                      // waves per workgroup
+// Narrow pixels.  Nearly all pixels keep a window of 2*lambda+1 hypotheses, so a
+// wave per line works with 7 of its 64 K slots.  Here lane j of a row holds the
+// hypothesis k of the pixel's window with k = j (mod 16): any window of up to 16
+// hypotheses fits, a window that moves needs no data movement, and the
+// neighbours k -+ 1 are the lanes j -+ 1 of the row (row_ror).  Lanes outside the
+// window hold kOut or more, which loses to m + P2: the terms of Eq. (8) outside
+// R(p - r) drop out without any masks, as long as the previous window and this
+// one with a hypothesis to each side lie within 16 consecutive hypotheses.  Where
+// they do not (a jump), a lane whose hypothesis changed is set to kOut first.
+//
+// Wide pixels (more than 14 hypotheses: the full-range ones).  Rows that are at
+// one take a second path, entered by the wave when any of its rows is: lane j
+// then holds the 2 NR hypotheses from lo + 2 NR j, two per register in packed
+// 16-bit arithmetic (0xFFFF outside the window), with one 16-byte load and store
+// per four registers.  Where the window starts elsewhere than the previous one,
+// or the previous or next pixel is narrow, the path costs go through a row of LDS
+// that has 0xFFFF on both sides (a narrow window takes one hypothesis more to each
+// side, hence at most 14).
+//
+// Lines.  The lines of a direction are taken as units of equal length: the
+// primary axis is the one the direction moves fastest along (the shorter one for
+// the diagonals), and unit x walks it from its entry side, starting at position
+// x of the other axis and, where the direction also moves along that one,
+// wrapping around its end.  A path starts (L = C) at the first step and at each
+// wrap, which is where the predecessor is outside the image.  A knight move
+// steps two along its primary axis: one set of units per parity.  A wave's four
+// rows take four neighbouring units, so they walk side by side.
+//
+// Metadata.  Lane j of a row holds what step j of the current block of 16 steps
+// needs (bounds, cell offset), decoded once, and a step reads it by a row
+// broadcast (row_newbcast) fused into the instruction that uses it; the next
+// block's is decoded and its successor's loads are in flight.  Ballots of the
+// decode say which steps have anything but narrow pixels in the middle of a path:
+// one bit test keeps the others to about 18 VALU for four lines.
+struct RowsArgs {
+    gptr<const uint16_t> cost;
+    gptr<const int64_t> off;
+    gptr<const int16_t> lo;
+    gptr<const int16_t> hi;
+    gptr<uint16_t> Lbuf;           // [npaths][dir_stride]
+    size_t dir_stride;
+    int H, W, N;
+    uint32_t P1, P2;
+    int npaths;
+    int wbase[kMaxPaths + 1];      // direction r owns waves [wbase[r], wbase[r+1])
+};
 
-// Entries of one LDS row: N + 2, padded so that the rows of the lines of a wave
-// (two per line) start on different banks.
-__host__ __device__ constexpr int b16_row(int N) { return (N + 2 + 15) / 16 * 16 + 8; }
+// The walk of direction (du, dv) as equal units.
+struct Walk {
+    bool pv;            // the primary axis is v
+    int step, dir;      // pixels per step along it, and its sign
+    int len, Q;         // lengths of the primary and the other axis
+    int dsec;           // movement along the other axis per step: -1, 0, 1
+    int units;          // Q for each parity of the primary axis
+};
 
-// Minimum over each group of G lanes (G = 16: a DPP row; 32: two rows), in
-// every lane of the group.
-template <int G>
-__device__ __forceinline__ uint32_t group_min(uint32_t v) {
-    v = min(v, dpp<0xB1>(UINT_MAX, v));           // quad_perm [1,0,3,2]
-    v = min(v, dpp<0x4E>(UINT_MAX, v));           // quad_perm [2,3,0,1]
-    v = min(v, dpp<0x141>(UINT_MAX, v));          // row_half_mirror
-    v = min(v, dpp<0x140>(UINT_MAX, v));          // row_mirror: the row's minimum
-    if constexpr (G == 32)                        // swap the rows of each 32-lane half
-        v = min(v, (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F));
-    return v;
+__host__ __device__ inline Walk make_walk(int H, int W, int du, int dv) {
+    const int au = du < 0 ? -du : du, av = dv < 0 ? -dv : dv;
+    Walk w;
+    w.pv = av > au || (av == au && H <= W);
+    w.step = av > au ? av : au;
+    w.dir = (w.pv ? dv : du) > 0 ? 1 : -1;
+    w.len = w.pv ? H : W;
+    w.Q = w.pv ? W : H;
+    w.dsec = w.pv ? du : dv;
+    w.units = w.Q * (w.step < w.len ? w.step : w.len);
+    return w;
 }
 
-template <int G, int KC, int DM, int DC>
-__device__ __forceinline__ void bounded_group_wave(const BoundedArgs& a, uint32_t b,
-                                                   uint32_t* lds) {
-    constexpr int kLines = 64 / G;                // lines per wave
-    const int lane = threadIdx.x & 63, sub = lane & (G - 1), grp = lane / G;
-    const int wave = threadIdx.x >> 6;
-    const int H = a.H, W = a.W, N = a.N;
-    const uint32_t P1 = a.P1, P2 = a.P2;
-    const int g = ((int)b * kB16Waves + wave) * kLines + grp;   // this group's line
-    const int nlines = a.lines.nlines;
-    LineInfo li{0, 0, 0, 0, 0, 0};
-    if (g < nlines) li = locate(a.lines, H, W, g);
-    // steps: the longest line of the wave (wave-uniform)
-    int steps = 0;
-#pragma unroll
-    for (int i = 0; i < kLines; ++i) steps = max(steps, __builtin_amdgcn_readlane(li.len, i * G));
-    if (steps == 0) return;
-    const int RP = b16_row(N);
-    uint32_t* const row0 = lds + (size_t)(wave * kLines + grp) * 2 * RP;
-    for (int i = sub; i < 2 * RP; i += G) row0[i] = 0xFFFF0000u;     // no step wrote it
-    const PixMeta* __restrict__ meta = a.meta;
-    const uint16_t* __restrict__ cost = a.cost;
-    uint16_t* __restrict__ out = a.Lbuf + (size_t)li.r * a.dir_stride;
-    const int last = max(li.len - 1, 0);
-    auto pix = [&](int step) {                    // steps past the line repeat its end
-        const int st = min(step, last);
-        return (uint32_t)((li.v0 + st * li.dv) * W + li.u0 + st * li.du);
-    };
-    PixMeta mb[DM];
-    uint32_t cb[DC][KC];
-    auto load_costs = [&](const PixMeta& pm, uint32_t (&c)[KC]) {
-        const int lo = pm.lohi & 0xFFFF, hi = pm.lohi >> 16;
-#pragma unroll
-        for (int j = 0; j < KC; ++j) {
-            const int k = lo + G * j + sub;
-            c[j] = k <= hi ? (uint32_t)cost[pm.base(N) + k] : 0u;
-        }
-    };
-#pragma unroll
-    for (int i = 0; i < DM; ++i) mb[i] = meta[in_vgpr(pix(i))];
-#pragma unroll
-    for (int i = 0; i < DC; ++i) load_costs(mb[i], cb[i]);
-
-    uint32_t m = 0;
-    for (int base = 0; base < steps; base += DM) {
-#pragma unroll
-        for (int i = 0; i < DM; ++i) {
-            const int step = base + i;            // wave-uniform
-            const PixMeta pm = mb[i];
-            const int lo = pm.lohi & 0xFFFF, hi = pm.lohi >> 16;
-            uint32_t C[KC];
-#pragma unroll
-            for (int j = 0; j < KC; ++j) C[j] = cb[i % DC][j];
-            // refill: the costs of step + DC (its meta arrived DM - DC steps ago),
-            // then the meta of step + DM
-            load_costs(mb[(i + DC) % DM], cb[i % DC]);
-            mb[i] = meta[in_vgpr(pix(step + DM))];
-            const bool live = step < li.len;
-            uint32_t* const prev = row0 + ((step + 1) & 1) * RP;    // written at step - 1
-            uint32_t* const cur = row0 + (step & 1) * RP;
-            const uint32_t tag = (uint32_t)(step - 1) << 16;
-            const uint32_t mP2 = m + P2;
-            uint32_t rmin = UINT_MAX;
-#pragma unroll
-            for (int j = 0; j < KC; ++j) {
-                const int k = lo + G * j + sub;
-                if (k <= hi) {
-                    uint32_t L;
-                    if (step == 0) {
-                        L = C[j];
-                    } else {
-                        const uint32_t e0 = prev[k + 1] - tag;      // k
-                        const uint32_t em = prev[k] - tag;          // k - 1
-                        const uint32_t ep = prev[k + 2] - tag;      // k + 1
-                        const uint32_t t = min(min(e0, min(em, ep) + P1), mP2);
-                        L = t + C[j] - m;
-                    }
-                    cur[k + 1] = L | ((uint32_t)step << 16);
-                    if (live) out[pm.base(N) + k] = (uint16_t)L;
-                    rmin = min(rmin, L);
-                }
-            }
-            m = group_min<G>(rmin);
-            // the next step reads what the other lanes of this wave wrote
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
+// The waves of the directions, four units each, and their prefix sums.
+inline void rows_waves(int H, int W, int npaths, int* wbase) {
+    int n = 0;
+    wbase[0] = 0;
+    for (int r = 0; r < kMaxPaths; ++r) {
+        if (r < npaths) n += (make_walk(H, W, kDirs[r][0], kDirs[r][1]).units + 3) / 4;
+        wbase[r + 1] = n;
     }
 }
 
-template <class Src, int G, int KC>
-__global__ __launch_bounds__(64 * kB16Waves) void sgm_bounded_group_kernel(Src src) {
-    __shared__ uint32_t lds[kB16Waves * (64 / G) * 2 * b16_row(KC * G)];
+// Lane j of every row takes lane I's value of its row.
+template <int I>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + I, 0xF, 0xF, true);
+}
+
+// The same in a register of its own, for values that are subtracted or shifted by:
+// the compiler folds a DPP operand into the reversed forms too (v_subrev,
+// v_lshrrev), which permute the other operand (measured).
+template <int I>
+__device__ __forceinline__ uint32_t row_value(uint32_t v) {
+    uint32_t x = row_bcast<I>(v);
+    asm("" : "+v"(x));
+    return x;
+}
+
+// Row rotations: the value of lane j - 1 and of lane j + 1 (mod 16).
+__device__ __forceinline__ uint32_t row_prev(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t row_next(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x12F, 0xF, 0xF, true);
+}
+
+// Minimum over each row of 16 lanes, in every lane of it (rotations by 8, 4, 2, 1).
+__device__ __forceinline__ uint32_t row_min(uint32_t v) {
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, true));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xF, 0xF, true));
+    return min(v, row_prev(v));
+}
+
+// What the four rows need of the 16 steps of a block: lane j of a row holds step
+// j of its line.
+struct RowsMeta {
+    uint32_t lo, hi;
+    uint32_t nlo2;          // -2 lo
+    uint32_t offb;          // byte offset of the pixel's first cell
+    int32_t w2;             // (hi - lo) * 2, or -1 for pixels the narrow path skips
+    uint32_t flags;         // kRowWide ...
+    // steps (bits 0..15) at which any of the rows has the flag
+    uint32_t wide, pre, conv, part, leave;     // pre: kRowStart or kRowJump
+};
+constexpr uint32_t kRowWide = 1,    // a wide pixel
+    kRowStart = 2,                  // the start of a path
+    kRowJump = 4,                   // windows too far apart for the lanes (see above)
+    kRowConv = 8,                   // wide, but not after a wide one from the same lo
+    kRowAfterWide = 16;             // the pixel before is a wide one
+
+// The steps at which any of the four rows has its bit set.
+__device__ __forceinline__ uint32_t any_row(uint64_t ballot) {
+    const uint32_t half = (uint32_t)ballot | (uint32_t)(ballot >> 32);
+    return (half | half >> 16) & 0xFFFFu;
+}
+
+constexpr int kRowsNarrow = 14;        // the widest window of the narrow path
+
+// Two 16-bit values per register.
+using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
+using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
+using u16x2 = unsigned short __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 as_u16x2(uint32_t x) { return __builtin_bit_cast(u16x2, x); }
+__device__ __forceinline__ uint32_t as_u32(u16x2 x) { return __builtin_bit_cast(uint32_t, x); }
+__device__ __forceinline__ uint32_t pk_min(uint32_t x, uint32_t y) {
+    return as_u32(__builtin_elementwise_min(as_u16x2(x), as_u16x2(y)));
+}
+__device__ __forceinline__ uint32_t pk_add(uint32_t x, uint32_t y) {
+    return as_u32(as_u16x2(x) + as_u16x2(y));
+}
+__device__ __forceinline__ uint32_t pk_sub(uint32_t x, uint32_t y) {
+    return as_u32(as_u16x2(x) - as_u16x2(y));
+}
+__device__ __forceinline__ uint32_t pk_add_sat(uint32_t x, uint32_t y) {
+    return as_u32(__builtin_elementwise_add_sat(as_u16x2(x), as_u16x2(y)));
+}
+// (x >> 16) | (y << 16): the high half of x and the low half of y.
+__device__ __forceinline__ uint32_t pk_next(uint32_t x, uint32_t y) {
+    return __builtin_amdgcn_alignbit(y, x, 16);
+}
+
+// LDS of one row's wide path costs: 16 lanes x 2 NR hypotheses, with as many
+// entries of 0xFFFF before and after them.
+template <int NR>
+constexpr int kRowsPad = 32 * NR;              // entries
+template <int NR>
+constexpr int kRowsLds = 3 * kRowsPad<NR>;
+
+template <int NR>
+__device__ __forceinline__ void bounded_rows_wave(const RowsArgs& a, int wave, uint16_t* lds) {
+    constexpr int B = 16;           // steps per block
+    constexpr int DW = 4;           // steps ahead that a wide pixel's costs are loaded
+    constexpr int PAD = kRowsPad<NR>;
+    const int lane = threadIdx.x & 63, j = lane & 15, row = lane >> 4;
+    const int H = a.H, W_ = a.W, N = a.N;
+    const uint32_t P1 = a.P1, P2 = a.P2;
+
+    // the wave's direction (constant indices: the record stays in registers)
+    int r = 0, wb = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxPaths; ++i)
+        if (i < a.npaths && wave >= a.wbase[i]) {
+            r = i;
+            wb = a.wbase[i];
+        }
+    const Walk wk = make_walk(H, W_, dir_u(r), dir_v(r));
+
+    const int x = (wave - wb) * 4 + row;                      // this row's unit
+    const int xq = min(x, wk.units - 1);
+    const int q = xq / wk.Q, sec0 = xq - q * wk.Q;            // parity, start
+    const int P = (wk.len - q + wk.step - 1) / wk.step;       // steps of this unit
+    const int steps = (wk.len + wk.step - 1) / wk.step;       // of the wave
+    const int Prow = x < wk.units ? P : 0;                    // none past the last unit
+
+    // Byte offsets are from a 4-byte boundary at or before the costs' first cell: whole
+    // aligned words of them are loaded for wide pixels, the last one at most two bytes
+    // past the last cell.  The descriptors drop every access outside the volumes (the
+    // costs may end at the last cell, which only the offsets know).
+    const uint64_t cbase = (uint64_t)(const uint16_t*)a.cost;
+    const uint32_t odd = (uint32_t)cbase & 2u;
+    const uint64_t cells = min((uint64_t)a.off[H * W_], (uint64_t)a.dir_stride);
+    const int32_t vol_bytes = (int32_t)(a.dir_stride * 2 + odd);
+    const int32_t cost_bytes = __builtin_amdgcn_readfirstlane((int32_t)(cells * 2 + odd));
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(cbase - odd), (short)0, (cost_bytes + 3) & ~3, 0x00020000);
+    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((uint64_t)((uint16_t*)a.Lbuf + (size_t)r * a.dir_stride) - odd), (short)0,
+        vol_bytes, 0x00020000);
+
+    // --- metadata of a block: loads, then the decode ---
+    int tau = j;                                              // this lane's step
+    int sec = sec0 + wk.dsec * (j % wk.Q);                    // and where it is
+    if (sec >= wk.Q) sec -= wk.Q;
+    if (sec < 0) sec += wk.Q;
+    const int adv = wk.dsec * (B % wk.Q);
+    struct Raw {
+        uint32_t off;
+        int lo, hi, sec, tau;
+    };
+    const uint32_t* __restrict__ off32 = (const uint32_t*)(const int64_t*)a.off;
+    const int16_t* __restrict__ plo = a.lo;
+    const int16_t* __restrict__ phi = a.hi;
+    auto load_raw = [&]() -> Raw {
+        const int st = q + wk.step * min(tau, P - 1);
+        const int pri = wk.dir > 0 ? st : wk.len - 1 - st;
+        const uint32_t p = (uint32_t)(wk.pv ? pri * W_ + sec : sec * W_ + pri);
+        Raw x;
+        x.off = off32[2 * (size_t)p];                         // the low half: < 2^30 cells
+        x.lo = plo[p];
+        x.hi = phi[p];
+        x.sec = sec;
+        x.tau = tau;
+        tau += B;
+        sec += adv;
+        if (sec >= wk.Q) sec -= wk.Q;
+        if (sec < 0) sec += wk.Q;
+        return x;
+    };
+    // prv: the block before (its last step precedes this one's first)
+    auto decode = [&](const Raw& x, const RowsMeta& prv) -> RowsMeta {
+        RowsMeta m;
+        // bounds outside the documented 0 <= lo <= hi < N are clamped into it
+        const int lo = clampi(x.lo, 0, N - 1), hi = clampi(x.hi, lo, N - 1);
+        const bool live = x.tau < Prow;
+        const bool start = x.tau == 0 || (wk.dsec > 0 && x.sec == 0) ||
+                           (wk.dsec < 0 && x.sec == wk.Q - 1);
+        const bool wide = live && hi - lo >= kRowsNarrow, skip = wide || !live;
+        m.lo = (uint32_t)lo;
+        m.hi = (uint32_t)hi;
+        m.nlo2 = 0u - 2u * (uint32_t)lo;
+        m.offb = x.off * 2 + odd;
+        m.w2 = skip ? -1 : (hi - lo) * 2;
+        const int pl = (int)dpp<0x111>(row_bcast<15>(prv.lo), m.lo);
+        const int ph = (int)dpp<0x111>(row_bcast<15>(prv.hi), m.hi);
+        const bool pwide = ph - pl >= kRowsNarrow;
+        const bool jump = !skip && !start && !pwide && max(ph, hi + 1) - min(pl, lo - 1) >= 16;
+        const bool conv = wide && !start && (!pwide || pl != lo);
+        m.flags = (wide ? kRowWide : 0) | (live && start ? kRowStart : 0) |
+                  (jump ? kRowJump : 0) | (conv ? kRowConv : 0) | (pwide ? kRowAfterWide : 0);
+        const uint64_t bw = __builtin_amdgcn_ballot_w64(wide);
+        m.wide = any_row(bw);
+        m.pre = any_row(__builtin_amdgcn_ballot_w64(jump || (live && start)));
+        m.conv = any_row(__builtin_amdgcn_ballot_w64(conv));
+        m.part = any_row(__builtin_amdgcn_ballot_w64(wide && (lo != 0 || hi != N - 1)));
+        // a narrow pixel follows (the last step of a block: perhaps)
+        m.leave = any_row(bw & ~(bw >> 1 & 0x7FFF7FFF7FFF7FFFull));
+        return m;
+    };
+
+    const uint32_t J = (uint32_t)j;
+    constexpr uint32_t kOut = 0x3FFF0000u;    // the cost of a lane outside the window
+    constexpr uint32_t kNowhere = 0x80000000u;            // an offset outside every volume
+    // --- prefetched 16 steps ahead: the lane's cell (A) and its cost (C) ---
+    uint32_t A[B], C[B];
+    bool in[B];
+    auto locate_cell = [&](const RowsMeta& m, auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const uint32_t o = (2 * J + row_bcast<i>(m.nlo2)) & 30u;
+        in[i] = (int)o <= (int)row_bcast<i>((uint32_t)m.w2);
+        uint32_t at = row_bcast<i>(m.offb) + o;
+        asm volatile("" : "+v"(at));          // in every lane: a broadcast that was folded into
+        A[i] = in[i] ? at : kNowhere;         // an add under a mask would read a masked lane
+    };
+    // Where a lane's prefetch reads: its cell, but in the row of a wide pixel a place
+    // all over its cells, so that their lines are in the cache when fetch_wide loads
+    // them (the values are not used).
+    auto spread = [&](const RowsMeta& m, auto ic, uint32_t ad) -> uint32_t {
+        constexpr int i = decltype(ic)::value;
+        const uint32_t w2 = 2 * (row_value<i>(m.hi) - row_value<i>(m.lo));
+        const uint32_t at = row_value<i>(m.offb) + min(4 * NR * J, w2);
+        return row_value<i>(m.flags) & kRowWide ? at : ad;
+    };
+    // --- the costs of a wide pixel: the words that hold the lane's cells ---
+    uint32_t CW[DW][NR + 1];
+    auto fetch_wide = [&](const RowsMeta& m, auto ic, auto slot) {
+        constexpr int i = decltype(ic)::value, sl = decltype(slot)::value;
+        const uint32_t ad = (row_value<i>(m.offb) + 4 * NR * J) & ~3u;
+        if constexpr (NR == 2) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rc, ad, 0, 0);
+            CW[sl][0] = v[0];
+            CW[sl][1] = v[1];
+        } else {
+#pragma unroll
+            for (int c = 0; c < NR; c += 4) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(rc, ad, 4 * c, 0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) CW[sl][c + e] = v[e];
+            }
+        }
+        CW[sl][NR] = __builtin_amdgcn_raw_buffer_load_b32(rc, ad, 4 * NR, 0);
+    };
+
+    uint16_t* const lrow = lds + row * kRowsLds<NR>;          // this row's entries
+    uint32_t MF[NR];                                          // full range: 0xFFFF past N
+#pragma unroll
+    for (int c = 0; c < NR; ++c) {
+        const int k = 2 * NR * j + 2 * c;
+        MF[c] = (k < N ? 0u : 0xFFFFu) | (k + 1 < N ? 0u : 0xFFFF0000u);
+        *(uint32_t*)(lrow + k) = ~0u;
+        *(uint32_t*)(lrow + 2 * PAD + k) = ~0u;
+    }
+
+    Raw raw = load_raw();
+    RowsMeta cur{};
+    cur = decode(raw, cur);
+    raw = load_raw();
+    RowsMeta nxt = decode(raw, cur);
+    raw = load_raw();
+    // (a store that the descriptor drops after each load, as in the loop: the waits for
+    // the loads count the accesses issued since, on the way that has the fewest)
+    static_for<B>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        locate_cell(cur, ic);
+        C[i] = __builtin_amdgcn_raw_buffer_load_b16(
+            rc, cur.wide & (1u << i) ? spread(cur, ic, A[i]) : A[i], 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)0, ro, kNowhere, 0, 0);
+    });
+    static_for<DW>([&](auto ic) {
+        if (cur.wide & (1u << decltype(ic)::value)) fetch_wide(cur, ic, ic);
+    });
+
+    uint32_t V = 0, m = 0;                    // the previous pixel's path costs, minimum
+    uint32_t Wp[NR];
+#pragma unroll
+    for (int c = 0; c < NR; ++c) Wp[c] = 0;
+    uint32_t last_lo = 0;                     // lo of the last step of the block before
+
+    auto step = [&](auto ic, uint32_t busy) {
+        constexpr int i = decltype(ic)::value;
+        constexpr uint32_t bit = 1u << i;
+        const uint32_t cost = in[i] ? C[i] : kOut;
+        const uint32_t ad = A[i];
+        locate_cell(nxt, ic);                 // the slot just consumed
+        auto prev_lo = [&] { return i > 0 ? row_value<(i + B - 1) % B>(cur.lo) : last_lo; };
+        if (__builtin_expect(cur.pre & bit, 0)) {
+            const uint32_t flags = row_value<i>(cur.flags);
+            const uint32_t lo = row_value<i>(cur.lo), pl = prev_lo();
+            const bool moved = lo - 1 + ((J + 1 - lo) & 15u) != pl + ((J - pl) & 15u);
+            if (moved && (flags & kRowJump)) V = kOut;
+            if (flags & kRowStart) {          // so that L = C
+                V = 0;
+                m = 0;
+#pragma unroll
+                for (int c = 0; c < NR; ++c) Wp[c] = 0;
+            }
+        }
+        const uint32_t side = V + P1;
+        const uint32_t nbr = min(row_prev(side), row_next(side));
+        const uint32_t t = min(min(V, nbr), m + P2);
+        const uint32_t L = t + (cost - m);
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)L, ro, ad, 0, 0);   // or nowhere
+        uint32_t Vn = L, rmin = L;
+        uint32_t next = A[i];
+        if (__builtin_expect(busy & bit, 0)) {
+          if (cur.wide & bit) {
+            const uint32_t flags = row_value<i>(cur.flags);
+            if (flags & kRowWide) {
+                const uint32_t offb = row_value<i>(cur.offb), lo = row_value<i>(cur.lo);
+                const uint32_t w = row_value<i>(cur.hi) - lo;
+                // the previous path costs from this window's first hypothesis on, and
+                // the one before it (at the start of a path: zeros)
+                uint32_t below = 0xFFFF0000u;
+                if (__builtin_expect(cur.conv & bit, 0) && (flags & kRowConv)) {
+                    const bool pw = (flags & kRowAfterWide) != 0;
+                    const uint32_t pl = prev_lo();
+                    uint32_t* const own = (uint32_t*)(lrow + PAD + 2 * NR * j);
+#pragma unroll
+                    for (int c = 0; c < NR; ++c) own[c] = pw ? Wp[c] : ~0u;
+                    if (!pw && V < 0x10000u) lrow[PAD + ((J - pl) & 15u)] = (uint16_t)V;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    const int d = clampi((int)lo - (int)pl, 1 - PAD, PAD - 1);
+                    __builtin_memcpy(Wp, lrow + PAD + d + 2 * NR * j, 4 * NR);
+                    below = (uint32_t)lrow[PAD + d - 1] << 16;
+                }
+                const uint32_t P11 = P1 | P1 << 16, mP2 = m + P2;
+                const uint32_t m2 = mP2 | mP2 << 16, mm2 = m | m << 16;
+                uint32_t Xw[NR], nb[NR + 1];
+#pragma unroll
+                for (int c = 0; c < NR; ++c) Xw[c] = pk_add_sat(Wp[c], P11);
+                nb[0] = pk_next(dpp<0x111>(pk_add_sat(below, P11), Xw[NR - 1]), Xw[0]);
+#pragma unroll
+                for (int c = 1; c < NR; ++c) nb[c] = pk_next(Xw[c - 1], Xw[c]);
+                nb[NR] = pk_next(Xw[NR - 1], dpp<0x101>(~0u, Xw[0]));
+                const uint32_t shift = (offb & 2u) * 8;
+                uint32_t out[NR], wm = ~0u;
+#pragma unroll
+                for (int c = 0; c < NR; ++c) out[c] = MF[c];
+                const bool part = __builtin_expect((cur.part & bit) != 0, 0);
+                if (part) {
+#pragma unroll
+                    for (int c = 0; c < NR; ++c) {
+                        const uint32_t k = 2 * NR * J + 2 * c;
+                        out[c] = (k <= w ? 0u : 0xFFFFu) | (k + 1 <= w ? 0u : 0xFFFF0000u);
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < NR; ++c) {
+                    const uint32_t cw = __builtin_amdgcn_alignbit(CW[i % DW][c + 1],
+                                                                  CW[i % DW][c], shift);
+                    const uint32_t tt = pk_min(pk_min(Wp[c], m2), pk_min(nb[c], nb[c + 1]));
+                    Wp[c] = pk_add(tt, pk_sub(cw, mm2)) | out[c];
+                    wm = pk_min(wm, Wp[c]);
+                }
+                rmin = min(wm & 0xFFFFu, wm >> 16);
+                // 2 NR cells per lane, the last lane's in pieces of 8, 4, 2, 1; of how
+                // many cells is wave-uniform unless some row is not at its full range
+                const uint32_t to = offb + 4 * NR * J;
+                auto store_cells = [&](int left, int last) {
+                    if (left >= 2 * NR) {
+                        if constexpr (NR == 2) {
+                            __builtin_amdgcn_raw_buffer_store_b64(u32x2{Wp[0], Wp[1]}, ro, to, 0,
+                                                                  0);
+                        } else {
+#pragma unroll
+                            for (int c = 0; c < NR; c += 4)
+                                __builtin_amdgcn_raw_buffer_store_b128(
+                                    u32x4{Wp[c], Wp[c + 1], Wp[c + 2], Wp[c + 3]}, ro, to, 4 * c,
+                                    0);
+                        }
+                    }
+                    const bool end = left > 0 && left < 2 * NR;
+                    uint32_t v[NR], at = to;
+#pragma unroll
+                    for (int e = 0; e < NR; ++e) v[e] = Wp[e];
+                    static_for<NR == 8 ? 3 : NR == 4 ? 2 : 1>([&](auto h) {
+                        constexpr int n = (NR >> 1) >> decltype(h)::value;    // registers
+                        if (last & (2 * n)) {
+                            if (end) {
+                                if constexpr (n == 4)
+                                    __builtin_amdgcn_raw_buffer_store_b128(
+                                        u32x4{v[0], v[1], v[2], v[3]}, ro, at, 0, 0);
+                                else if constexpr (n == 2)
+                                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{v[0], v[1]}, ro,
+                                                                          at, 0, 0);
+                                else
+                                    __builtin_amdgcn_raw_buffer_store_b32(v[0], ro, at, 0, 0);
+                            }
+                            at += 4 * n;
+#pragma unroll
+                            for (int e = 0; e < n; ++e) v[e] = v[e + n];
+                        }
+                    });
+                    if (last & 1)
+                        if (end)
+                            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v[0], ro, at, 0, 0);
+                };
+                if (part) store_cells((int)w + 1 - 2 * NR * j, (int)w + 1 - 2 * NR * j);
+                else store_cells(N - 2 * NR * j, N);
+                if (__builtin_expect(cur.leave & bit, 0)) {   // a row's next pixel is narrow
+                    const uint32_t nl = row_value<(i + 1) % B>(i + 1 < B ? cur.lo : nxt.lo);
+                    uint32_t* const own = (uint32_t*)(lrow + PAD + 2 * NR * j);
+#pragma unroll
+                    for (int c = 0; c < NR; ++c) own[c] = Wp[c];
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    // hypotheses lo' - 1 .. lo' + 14 of the next window
+                    const int d = (int)(nl - 1 + ((J + 1 - nl) & 15u) - lo);
+                    Vn = lrow[PAD + clampi(d, -PAD, 2 * PAD - 1)];
+                }
+            }
+          }
+          if (nxt.wide & bit) next = spread(nxt, ic, next);
+          const RowsMeta& ahead = i + DW < B ? cur : nxt;
+          if (ahead.wide & (1u << (i + DW) % B))
+              fetch_wide(ahead, std::integral_constant<int, (i + DW) % B>(),
+                         std::integral_constant<int, i % DW>());
+        }
+        C[i] = __builtin_amdgcn_raw_buffer_load_b16(rc, next, 0, 0);
+        V = Vn;
+        m = row_min(rmin);
+    };
+    for (int base = 0; base < steps; base += B) {
+        // steps that are at a wide pixel or prefetch for one
+        const uint32_t busy = cur.wide | nxt.wide | cur.wide >> DW | nxt.wide << (B - DW);
+        static_for<B>([&](auto ic) {
+            step(ic, busy);
+        });
+        last_lo = row_value<B - 1>(cur.lo);
+        cur = nxt;
+        nxt = decode(raw, cur);
+        raw = load_raw();
+    }
+}
+
+template <class Src, int NR>
+__global__ __launch_bounds__(64 * kWavesPerBlock, NR <= 4 ? 4 : 2) void sgm_bounded_rows_kernel(Src src) {
+    __shared__ __align__(16) uint16_t lds[kWavesPerBlock * 4 * kRowsLds<NR>];
     for (uint32_t vb = blockIdx.x; vb < src.total; vb += gridDim.x) {
         uint32_t b;
-        const BoundedArgs& a = member(src, vb, b);
-        __syncthreads();                          // the previous block's rows are done
-        bounded_group_wave<G, KC, 8, 4>(a, b, lds);
+        const RowsArgs& a = member(src, vb, b);
+        const int wv = threadIdx.x >> 6;
+        const int w = __builtin_amdgcn_readfirstlane(b * kWavesPerBlock + wv);
+        if (w >= a.wbase[kMaxPaths]) continue;        // wave-uniform
+        bounded_rows_wave<NR>(a, w, lds + wv * 4 * kRowsLds<NR>);
     }
 }
 
@@ -1189,45 +1599,13 @@ hipError_t bounded_variant(Runner& r, const std::vector<BoundedArgs>& args,
     return bounded_depth_variant<K, 16>(r, args, blocks, buf);
 }
 
-template <int G, int KC>
-hipError_t bounded_group_variant(Runner& r, const std::vector<BoundedArgs>& args) {
+template <int NR>
+hipError_t bounded_rows(Runner& r, const std::vector<RowsArgs>& args) {
     std::vector<uint32_t> blocks;
-    for (const BoundedArgs& a : args)
-        blocks.push_back(div_up(a.lines.base[a.lines.npaths], kB16Waves * (64 / G)));
-    return launch(r, kStSgmFinal, sgm_bounded_group_kernel<Single<BoundedArgs>, G, KC>,
-                  sgm_bounded_group_kernel<Group<BoundedArgs>, G, KC>, args, blocks,
-                  64 * kB16Waves);
-}
-
-// Chunks per line (hypotheses / G) rounded up to the compiled variants.
-int bounded_chunks(int N, int G) {
-    const int c = (N + G - 1) / G;
-    if (G == 16) {
-        for (int v : {2, 4, 7, 10, 13}) if (c <= v) return v;
-        return 16;
-    }
-    for (int v : {1, 2, 4, 6}) if (c <= v) return v;
-    return 8;
-}
-
-hipError_t bounded_group(Runner& r, int G, int KC, const std::vector<BoundedArgs>& args) {
-    if (G == 16) {
-        switch (KC) {
-            case 2: return bounded_group_variant<16, 2>(r, args);
-            case 4: return bounded_group_variant<16, 4>(r, args);
-            case 7: return bounded_group_variant<16, 7>(r, args);
-            case 10: return bounded_group_variant<16, 10>(r, args);
-            case 13: return bounded_group_variant<16, 13>(r, args);
-            default: return bounded_group_variant<16, 16>(r, args);
-        }
-    }
-    switch (KC) {
-        case 1: return bounded_group_variant<32, 1>(r, args);
-        case 2: return bounded_group_variant<32, 2>(r, args);
-        case 4: return bounded_group_variant<32, 4>(r, args);
-        case 6: return bounded_group_variant<32, 6>(r, args);
-        default: return bounded_group_variant<32, 8>(r, args);
-    }
+    for (const RowsArgs& a : args) blocks.push_back(div_up(a.wbase[kMaxPaths], kWavesPerBlock));
+    return launch(r, kStSgmFinal, sgm_bounded_rows_kernel<Single<RowsArgs>, NR>,
+                  sgm_bounded_rows_kernel<Group<RowsArgs>, NR>, args, blocks,
+                  64 * kWavesPerBlock);
 }
 
 hipError_t bounded_k(Runner& r, int K, const std::vector<BoundedArgs>& args,
@@ -1423,11 +1801,26 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
     std::vector<uint32_t> meta_blocks;
     std::vector<BoundedArgs> paths[4];
     std::vector<uint32_t> path_blocks[4];
-    // G lanes per line: [chunks per line] of the compiled variants (at most 16)
-    const int G = r.tune.bounded_lanes;
-    std::vector<BoundedArgs> grouped[17];
+    std::vector<RowsArgs> rows[3];                 // up to 64, 128, 256 hypotheses
     std::vector<BsumArgs> sums[2][2];              // [16/32-bit sums][8/16 paths]
     std::vector<uint32_t> sum_blocks[2][2];
+    // Four lines per wave, or one.  A step of four lines costs the GPU less than half of
+    // what four steps of one do, but takes about twice as long as one of those (every
+    // pixel of a wave waits for its widest), so it needs lines enough beside the
+    // longest one: all path steps over the steps of the longest line.  Bounded paths
+    // in us, one line per wave against four, 12 % full-range pixels: 512x512, N = 100
+    // on the benchmark bounds (4,096) 199 / 219; 640x640 (5,120) 299 / 202; 512x512
+    // with 16 paths (8,192) 382 / 254; 1080x1920, N = 96 (8,640) 1468 / 664.  Beyond
+    // 128 hypotheses a lane of the one-line form holds three or four: N = 200, 256x256
+    // (2,048) 94 / 95, 384x384 (3,072) 190 / 141, 375x450 with 16 paths 458 / 181.
+    uint64_t steps = 0, longest = 1;
+    int widest = 0;
+    for (const Job* j : jobs) {
+        steps += (uint64_t)j->H * j->W * j->prm.sgm_final.npaths;
+        longest = std::max(longest, (uint64_t)std::max(j->H, j->W));
+        widest = std::max(widest, j->N);
+    }
+    const bool many = r.tune.bounded_lanes < 64 || steps > longest * (widest > 128 ? 2300 : 4500);
     for (const Job* j : jobs) {
         const int H = j->H, W = j->W, N = j->N;
         const size_t HW = (size_t)H * W;
@@ -1436,24 +1829,37 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
         uint16_t* Lbuf = (uint16_t*)((char*)j->sgm_ws + round256(HW * sizeof(PixMeta)));
         const size_t dir_stride = HW * N;          // worst-case cells per direction
 
-        meta.push_back(MetaArgs{j->offsets, j->lo, j->hi, pm, (int)HW, N});
-        meta_blocks.push_back(div_up(HW, 256));
-
-        BoundedArgs b{};
-        b.cost = j->cost;
-        b.meta = pm;
-        b.Lbuf = Lbuf;
-        b.dir_stride = dir_stride;
-        b.lines = make_lines(H, W, sp.npaths);
-        b.units = make_units(b.lines, H, W);
-        b.H = H;
-        b.W = W;
-        b.N = N;
-        b.P1 = (uint32_t)sp.P1;
-        b.P2 = (uint32_t)sp.P2;
-        if (G == 16 || G == 32) {
-            grouped[bounded_chunks(N, G)].push_back(b);
+        if (many && r.tune.bounded_offsets == 32 && dir_stride * 2 + 4 <= (size_t)INT32_MAX) {
+            RowsArgs w{};
+            w.cost = j->cost;
+            w.off = j->offsets;
+            w.lo = j->lo;
+            w.hi = j->hi;
+            w.Lbuf = Lbuf;
+            w.dir_stride = dir_stride;
+            w.H = H;
+            w.W = W;
+            w.N = N;
+            w.P1 = (uint32_t)sp.P1;
+            w.P2 = (uint32_t)sp.P2;
+            w.npaths = sp.npaths;
+            rows_waves(H, W, sp.npaths, w.wbase);
+            rows[N <= 64 ? 0 : N <= 128 ? 1 : 2].push_back(w);
         } else {
+            meta.push_back(MetaArgs{j->offsets, j->lo, j->hi, pm, (int)HW, N});
+            meta_blocks.push_back(div_up(HW, 256));
+            BoundedArgs b{};
+            b.cost = j->cost;
+            b.meta = pm;
+            b.Lbuf = Lbuf;
+            b.dir_stride = dir_stride;
+            b.lines = make_lines(H, W, sp.npaths);
+            b.units = make_units(b.lines, H, W);
+            b.H = H;
+            b.W = W;
+            b.N = N;
+            b.P1 = (uint32_t)sp.P1;
+            b.P2 = (uint32_t)sp.P2;
             const int K = (N + 63) / 64 - 1;
             paths[K].push_back(b);
             path_blocks[K].push_back(div_up(b.units.nunits, kWavesPerBlock));
@@ -1470,18 +1876,19 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
         sums[sb][np16].push_back(s);
         sum_blocks[sb][np16].push_back(s.nblk);
     }
-    hipError_t e = launch(r, kStSgmFinal, pix_meta_kernel<Single<MetaArgs>>,
-                          pix_meta_kernel<Group<MetaArgs>>, meta, meta_blocks, 256);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    if (!meta.empty() &&
+        (e = launch(r, kStSgmFinal, pix_meta_kernel<Single<MetaArgs>>,
+                    pix_meta_kernel<Group<MetaArgs>>, meta, meta_blocks, 256)) != hipSuccess)
+        return e;
     for (int K = 0; K < 4; ++K) {
         if (paths[K].empty()) continue;
         e = bounded_k(r, K + 1, paths[K], path_blocks[K]);
         if (e != hipSuccess) return e;
     }
-    for (int c = 1; c <= 16; ++c) {
-        if (grouped[c].empty()) continue;
-        if ((e = bounded_group(r, G, c, grouped[c])) != hipSuccess) return e;
-    }
+    if (!rows[0].empty() && (e = bounded_rows<2>(r, rows[0])) != hipSuccess) return e;
+    if (!rows[1].empty() && (e = bounded_rows<4>(r, rows[1])) != hipSuccess) return e;
+    if (!rows[2].empty() && (e = bounded_rows<8>(r, rows[2])) != hipSuccess) return e;
     using BA = BsumArgs;
     if (!sums[0][0].empty() &&
         (e = launch(r, kStSgmFinal, bounded_sum_kernel<Single<BA>, uint16_t, 8>,
