@@ -3,15 +3,17 @@
 //
 // Work is flattened over the cells of the CSR volume so that pixels whose range
 // is the full hypothesis set and pixels with a 2*lambda+1 window share the
-// machine evenly; a cell finds its pixel by binary search over offsets staged in
-// LDS.  Consecutive threads handle consecutive hypotheses of one pixel and then
-// the next pixel of the row, so the bilinear taps of a view are read from a
-// narrow band of two rows (L1/L2 resident) and the cost writes are coalesced.
+// machine evenly; a cell, or a hypothesis of a few adjacent pixels, is found by binary
+// search over offsets staged in LDS.  Consecutive threads handle consecutive
+// hypotheses and then the next pixels of the row, so the taps of a view are read from
+// a narrow band of rows (L1/L2 resident) and the cost writes are close together.
 //
 // The view loop runs t outer, s inner, float32, with the shift of each view and
 // hypothesis rounded once: this is the precision the quantised integer cost is
 // decided in.  The reference view contributes exactly +0 and is skipped.
 #include "lf_internal.h"
+
+#include <type_traits>
 
 namespace lf {
 namespace {
@@ -36,55 +38,54 @@ __device__ __forceinline__ int find_pixel(const int64_t* s_off, int np, int64_t 
 // window cost the same per cell and no workgroup is a straggler.  The number of
 // slices is only known on the device (the last offset), so a light field gets
 // nblk workgroups sized for its worst case, and workgroup b walks the slices
-// b, b + nblk, ... that exist.  The first pixel of a slice is found by binary
-// search over the offsets; the offsets and lower bounds of the slice's pixels
-// are staged in LDS, and each cell finds its pixel there.  Consecutive threads
-// take consecutive cells (consecutive hypotheses of a pixel, then the next
-// pixel).
+// b, b + nblk, ... that exist.  The first pixel of a slice is searched for over
+// the offsets; the offsets and lower bounds of the slice's pixels are staged in LDS.
 //
-// Per view the two taps of a bilinear row, (x0, x0+1), are fetched by one 8-byte
-// load (the view pointer is only 4-byte aligned, which global loads allow):
-// that halves the gather instructions, whose issue rate -- not bytes -- bounds
-// this kernel.  At the image edges a tap is clamped; the pair then starts at
-// min(x_a, W-2) and each tap picks its element of the pair.
-template <typename T>
-struct Pair {
-    float lo, hi;
-};
+// What bounds this kernel is the issue of its scattered gathers (about four lanes a
+// cycle per CU, whatever their width up to 16 bytes), then its VALU.  So a slice's
+// pixels form groups of G horizontally adjacent ones: at one hypothesis a view shifts
+// them alike, and one load of G + 1 elements per tap row (and channel) serves them all.
+// The copy of 8-bit colour views interleaves the channels of a pixel in a word.
 
-template <typename T>
-__device__ __forceinline__ Pair<T> ld_pair(const T* p) {
-    if constexpr (sizeof(T) == 4) {
-        float2 v;
-        __builtin_memcpy(&v, p, 8);
-        return Pair<T>{v.x, v.y};
-    } else {
-        uint16_t v;
-        __builtin_memcpy(&v, p, 2);
-        return Pair<T>{(float)(v & 0xFF), (float)(v >> 8)};
-    }
+// Pixels per group.  A larger group has fewer loads per cell, a wider hull of its pixels'
+// ranges (on the benchmark bounds 1, 3, 5 pixels: 1.0, 2.0, 2.6 cells per hypothesis of
+// the hull) and so more arithmetic per cell.  Float views are bound by the loads: 3,
+// what 16 bytes hold.  8-bit grayscale ones by both: 3 (338 us; 4 or 5 with 8-byte
+// loads 418 us, one cell per thread with four 2-byte loads 512 us; 9x9x512^2, N = 100).
+// 8-bit colour ones by the arithmetic of three channels: 1 (625 us; 2 and 3 pixels
+// 916 and 1232 us, the planes apart 1870 us; the same size).
+template <typename T, int C>
+constexpr int kGroupOf = sizeof(T) == 4 ? 3 : C == 1 ? 3 : 1;
+
+// Views with a replicated edge: padded (y', x') holds the view at (clamp(y' - 1),
+// clamp(x' - L)), y' < H + 2, x' < W + P (one row above and below, L >= G columns left,
+// P - L right).  With it, the two clamped taps of a bilinear row, (clamp(X),
+// clamp(X+1)), are always the two consecutive elements starting at clamp(X, -1, W-1) +
+// L -- one load, no edge cases, and the same values (so the same float32 sums) as
+// clamping each tap; and the taps of the pixels g = 1 .. G-1 to the right, (clamp(X+g),
+// clamp(X+g+1)), are always elements g, g+1 of the G+1 starting at clamp(X, -L, W-1) + L
+// (X outside that range reads replicas).
+constexpr int kPadT = 1;
+constexpr int kPadL = 3;
+static_assert(kPadW == 2 * kPadL && kPadH == 2, "the view copy's margins");
+// Columns of the copy.  Single-byte rows of all but small images get 8 more: the bottom
+// taps of 512-column rows 518 bytes apart conflict with the top ones in the cache
+// (376 us of 9x9x512^2, N = 100; 347, 340 and 338 with rows of 522, 524 and 526).  Fits
+// the workspace, which is of floats, and a row of views of 2^31 bytes stays below 2^32.
+__host__ __device__ __forceinline__ int copy_width(int H, int W, size_t elem) {
+    return W + kPadW + (elem == 1 && H >= 8 && W >= 64 ? 8 : 0);
 }
-
-// Pixels per group of the grayscale float l2 cost (see l2_slices).
-constexpr int kGroup = 3;
-
-// Views with a replicated edge: padded (y', x') holds the view at
-// (clamp(y' - 1), clamp(x' - kGroup)), y' < H + 2, x' < W + 2 kGroup (one row
-// above and below, kGroup columns left and right).  With it, the two clamped
-// taps of a bilinear row, (clamp(X), clamp(X+1)), are always the two consecutive
-// elements starting at clamp(X, -1, W-1) + kGroup -- one 8-byte load, no edge
-// cases, and the same values (so the same float32 sums) as clamping each tap;
-// and the taps of the pixels g = 1 .. kGroup-1 to the right, (clamp(X+g),
-// clamp(X+g+1)), are always elements g, g+1 of the kGroup+1 starting at
-// clamp(X, -kGroup, W-1) + kGroup (X outside that range reads replicas).
-constexpr int kPadL = kGroup, kPadT = 1;
-static_assert(kPadW == 2 * kGroup && kPadH == 2, "view copy margins");
 
 struct PadArgs {
     gptr<const void> src;          // [planes][H][pitch] (a view is C planes)
-    gptr<void> dst;                // [planes][H + 2][W + 2 kGroup]
+    gptr<void> dst;                // [planes][H + 2][W + P]
     int H, W, pitch;
 };
+
+// Element of the copy at x from the three planes' rows of an 8-bit colour view.
+__device__ __forceinline__ uint32_t rgb_word(const uint8_t* r, size_t plane, int x) {
+    return (uint32_t)r[x] | (uint32_t)r[plane + x] << 8 | (uint32_t)r[2 * plane + x] << 16;
+}
 
 // A workgroup copies kPadRows padded rows of one plane: block b is rows
 // kPadRows * (b % g) .. of plane b / g (g row groups per plane).  Each thread
@@ -92,32 +93,36 @@ struct PadArgs {
 // stores them, so that many loads are in flight.
 constexpr int kPadRows = 4;
 
-template <class Src, typename T>
+// kRGB: 8-bit colour views, copied [views][H + 2][W + P] with a pixel's channels
+// in bytes 0..2 of a word.
+template <class Src, typename T, bool kRGB>
 __global__ __launch_bounds__(kThreads) void pad_views_kernel(Src src) {
+    using E = typename std::conditional<kRGB, uint32_t, T>::type;
     for (uint32_t vb = blockIdx.x; vb < src.total; vb += gridDim.x) {
         uint32_t b;
         const PadArgs& a = member(src, vb, b);
-        const int Hp = a.H + kPadH, Wp = a.W + kPadW;
+        const int Hp = a.H + kPadH, Wp = copy_width(a.H, a.W, sizeof(E));
         const int g = (Hp + kPadRows - 1) / kPadRows;
         const int z = (int)(b / (uint32_t)g);
         const int y0 = ((int)b - z * g) * kPadRows;
         for (int xb = 0; xb < Wp; xb += 3 * kThreads) {
-            T v[kPadRows][3];
+            E v[kPadRows][3];
 #pragma unroll
             for (int r = 0; r < kPadRows; ++r) {
                 const T* __restrict__ row =
-                    (const T*)a.src +
-                    ((size_t)z * a.H + clampi(y0 + r - kPadT, 0, a.H - 1)) * a.pitch;
+                    (const T*)a.src + ((size_t)z * (kRGB ? 3 : 1) * a.H +
+                                       clampi(y0 + r - kPadT, 0, a.H - 1)) * a.pitch;
 #pragma unroll
                 for (int e = 0; e < 3; ++e) {
-                    const int x = xb + e * kThreads + (int)threadIdx.x;
-                    v[r][e] = row[clampi(x - kPadL, 0, a.W - 1)];
+                    const int x = clampi(xb + e * kThreads + (int)threadIdx.x - kPadL, 0, a.W - 1);
+                    if constexpr (kRGB) v[r][e] = rgb_word(row, (size_t)a.H * a.pitch, x);
+                    else v[r][e] = row[x];
                 }
             }
 #pragma unroll
             for (int r = 0; r < kPadRows; ++r) {
                 if (y0 + r >= Hp) break;
-                T* __restrict__ out = (T*)a.dst + ((size_t)z * Hp + y0 + r) * Wp;
+                E* __restrict__ out = (E*)a.dst + ((size_t)z * Hp + y0 + r) * Wp;
 #pragma unroll
                 for (int e = 0; e < 3; ++e) {
                     const int x = xb + e * kThreads + (int)threadIdx.x;
@@ -129,7 +134,8 @@ __global__ __launch_bounds__(kThreads) void pad_views_kernel(Src src) {
 }
 
 struct L2Args {
-    gptr<const void> views;        // padded: [T][S][C][H + 2][W + 2 kGroup]
+    gptr<const void> views;        // padded: [T][S][C][H + 2][W + P], 8-bit colour ones
+                                   // [T][S][H + 2][W + P] words
     gptr<const float> hyp;
     gptr<const int16_t> lo;
     gptr<const int64_t> off;       // [H*W + 1]
@@ -141,75 +147,98 @@ struct L2Args {
     uint32_t nblk;            // workgroups of this light field
 };
 
-// kGroup + 1 consecutive elements of a padded float view row, one load.
-struct Row {
-    float e[kGroup + 1];
+// The taps of a group of G pixels in one tap row at p: n = G + 1 consecutive elements
+// per channel, or the first G of them, one load per plane (planes `plane` bytes apart).
+template <int C, int n>
+struct Taps {
+    float e[C][n];
 };
-__device__ __forceinline__ Row ld_row(const float* p) {
-    Row r;
-    __builtin_memcpy(&r, p, sizeof(Row));
+template <typename T, int C, int n>
+__device__ __forceinline__ Taps<C, n> ld_taps(const char* __restrict__ p, uint32_t plane) {
+    Taps<C, n> r;
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) __builtin_memcpy(r.e[c], p + (size_t)c * plane, 4 * n);
+    } else if constexpr (C == 1) {
+        static_assert(n <= 4, "one word");
+        uint32_t w;
+        __builtin_memcpy(&w, p, 4);
+#pragma unroll
+        for (int g = 0; g < n; ++g) r.e[0][g] = (float)(w >> (8 * g) & 0xFF);
+    } else {
+        uint32_t w[n];
+        __builtin_memcpy(w, p, 4 * n);
+#pragma unroll
+        for (int g = 0; g < n; ++g)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) r.e[c][g] = (float)(w[g] >> (8 * c) & 0xFF);
+    }
     return r;
 }
 
-// Block-wide exclusive prefix sum of cnt(i) over i in [0, np) into s_pre[0..np]
-// (s_pre[np] = the total); thread t owns the E consecutive entries from t*E.
-template <class Cnt>
-__device__ __forceinline__ void block_prefix(int np, Cnt cnt, int* s_pre, int* s_tmp) {
-    const int E = (np + kThreads - 1) / kThreads;
-    int local = 0;
-    for (int e = 0; e < E; ++e) {
-        const int i = threadIdx.x * E + e;
-        if (i < np) local += cnt(i);
-    }
-    s_tmp[threadIdx.x] = local;
-    __syncthreads();
-    if (threadIdx.x < 64) {                           // wave 0 scans the 256 sums
-        const int l = threadIdx.x;
-        const int v0 = s_tmp[4 * l], v1 = s_tmp[4 * l + 1], v2 = s_tmp[4 * l + 2],
-                  v3 = s_tmp[4 * l + 3];
-        const int own = v0 + v1 + v2 + v3;
-        int inc = own;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int n = __shfl_up(inc, o);
-            if (l >= o) inc += n;
-        }
-        const int ex = inc - own;
-        s_tmp[4 * l] = ex;
-        s_tmp[4 * l + 1] = ex + v0;
-        s_tmp[4 * l + 2] = ex + v0 + v1;
-        s_tmp[4 * l + 3] = ex + v0 + v1 + v2;
-        if (l == 63) s_pre[np] = inc;
-    }
-    __syncthreads();
-    int run = s_tmp[threadIdx.x];
-    for (int e = 0; e < E; ++e) {
-        const int i = threadIdx.x * E + e;
-        if (i < np) {
-            s_pre[i] = run;
-            run += cnt(i);
-        }
-    }
-    __syncthreads();
+// The correctly rounded square root of 0 and of every x in [2^-100, 2^100] (one
+// Newton step in fused arithmetic from the reciprocal square root; compared with
+// sqrtf on all 1.7e9 floats of the range): 6 instructions for the library's 17.
+constexpr float kRootMin = 0x1p-100f, kRootMax = 0x1p100f;
+__device__ __forceinline__ float root(float x) {
+    const float y = __builtin_amdgcn_rsqf(fmaxf(x, kRootMin));
+    const float s = x * y, h = 0.5f * y;
+    return fmaf(fmaf(-s, s, x), h, s);
 }
 
+// Exclusive prefix sum of one value per thread over the workgroup; *total its sum.
+__device__ __forceinline__ uint32_t block_prefix(uint32_t own, uint32_t* s_wave, uint32_t* total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t inc = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t n = __shfl_up(inc, o);
+        if (lane >= o) inc += n;
+    }
+    if (lane == 63) s_wave[wave] = inc;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) {
+        const uint32_t x = s_wave[w];
+        if (w < wave) before += x;
+        all += x;
+    }
+    *total = all;
+    return before + inc - own;
+}
+
+// LDS of one slice's pixels and groups.
+template <int CPT>
+struct SliceLds {
+    int rel[kThreads * CPT + 1];       // a pixel's first cell, from the slice's first
+    int16_t lo[kThreads * CPT];
+    uint32_t pre[kThreads * CPT];      // per group: items of the groups before it,
+    uint32_t uv[kThreads * CPT];       // its first pixel's u | v << 16,
+    uint32_t rec[kThreads * CPT];      // that pixel's index | pixels << 12 | first k << 16
+    uint32_t wave[kThreads / 64];
+    int np;
+};
+
 template <typename T, int CPT, bool Walk, int C>
-__device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, int64_t* s_off, int* s_lo,
-                                          int* s_p, int* s_pre, int* s_tmp) {
-    // float grayscale views: the cells of two horizontally adjacent pixels at one
-    // hypothesis share their loads (see below)
-    constexpr bool kPairs = sizeof(T) == 4 && C == 1;
-    constexpr int kChunk = kThreads * CPT;
+__device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<CPT>& sl) {
+    constexpr int kChunk = kThreads * CPT, G = kGroupOf<T, C>;
+    // planes of a view in the copy, bytes of an element
+    constexpr int CP = sizeof(T) == 1 && C == 3 ? 1 : C;
+    constexpr int kElem = sizeof(T) == 1 && C == 3 ? 4 : (int)sizeof(T);
+    static_assert(G <= kPadL, "the group's taps lie inside the margins");
     const int S = a.S, T_ = a.T, H = a.H, W = a.W, N = a.N;
-    const int Wp = W + kPadW;
+    const int Wp = copy_width(H, W, kElem);
     const int16_t* __restrict__ lo = a.lo;
     const int64_t* __restrict__ off = a.off;
     const int HW = H * W;
     const int64_t total = min(off[HW], a.cap_cells);
     const int sh = (S - 1) / 2, th = (T_ - 1) / 2;
-    const uint32_t vstride = (uint32_t)(H + kPadH) * Wp;
-    const T* __restrict__ views = (const T*)a.views;
-    const T* __restrict__ refv = views + ((size_t)th * S + sh) * C * vstride;
+    const uint32_t row = (uint32_t)Wp * kElem, plane = (uint32_t)(H + kPadH) * row;
+    const uint32_t vw_stride = (uint32_t)(H + kPadH) * Wp * CP;
+    const uint32_t vbytes = plane * CP;            // of a view: below 2^32
+    const char* __restrict__ views = (const char*)(const void*)a.views;
+    auto view_at = [&](int t, int s) { return views + ((size_t)t * S + s) * vbytes; };
 
     auto store = [&](int64_t c, float acc) {
         const float q = rintf(a.alpha * acc);
@@ -217,132 +246,78 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, int64_t* 
         if (a.cost_f32) a.cost_f32[c] = acc;
     };
 
-    // Eq. (12) for one cell: pixel (u, v), hypothesis d, over the views t outer,
-    // s inner.  One view of row t takes taps at horizontal fraction fx from the
-    // rows rt and rt + Wp.  Two cases skip taps that are weighted by an exact 0,
-    // since fma(0, b - a, a) is a exactly: the reference row of views (t = t_hat,
-    // flat: fy = 0, no bottom taps) and the reference column (s = s_hat, col:
-    // fx = 0, only the left tap of each row).  Each case is its own branch-free
-    // copy of the loop body.
-    auto cell = [&](int u, int v, float d) -> float {
-        float ref[C];
+    // Eq. (12) for the G pixels (u + g, v) at one hypothesis d, over the views t
+    // outer, s inner; one view of row t takes taps at horizontal fraction fx from two
+    // rows Wp apart.  Pixel g's taps are pixel 0's moved by g elements.  Two cases
+    // skip taps that are weighted by an exact 0, since fma(0, b - a, a) is a exactly:
+    // the reference row of views (t = t_hat, flat: fy = 0, no bottom taps) and the
+    // reference column (s = s_hat, col: fx = 0, only the left tap of each row).  Each
+    // case is its own branch-free copy of the loop body.
+    // kRoot: the colour norm by root(), whose range the caller looks after: lim[] takes
+    // the smallest and largest squared norm other than 0 (as bits, the smallest less 1).
+    auto group = [&](int u, int v, float d, float (&acc)[G], uint32_t (&lim)[2], auto kRoot) {
+        const Taps<C, G> ref = ld_taps<T, C, G>(
+            view_at(th, sh) + ((uint32_t)(v + kPadT) * Wp + u + kPadL) * kElem, plane);
 #pragma unroll
-        for (int c = 0; c < C; ++c)
-            ref[c] = ld(refv + (uint32_t)c * vstride + (uint32_t)(v + kPadT) * Wp + u + kPadL);
-        float acc = 0.0f;
-        auto view = [&](const T* __restrict__ vt, uint32_t rt, float fy, int s, bool flat,
-                        bool col) {
+        for (int g = 0; g < G; ++g) acc[g] = 0.0f;
+        constexpr std::true_type yes;
+        constexpr std::false_type no;
+        auto view = [&](const char* __restrict__ rt, float fy, int s, auto kFlat, auto kCol) {
             const float shx = (float)(sh - s) * d;
             const float x0 = floorf(shx);
             const float fx = shx - x0;
-            const uint32_t o = rt + (uint32_t)(clampi(u + (int)x0, -1, W - 1) + kPadL);
-            float sq = 0.0f, dist = 0.0f;
+            const char* __restrict__ vw = rt + (size_t)((uint32_t)s * vw_stride) * kElem +
+                                          (uint32_t)(clampi(u + (int)x0, -kPadL, W - 1) + kPadL) * kElem;
+            constexpr int n = decltype(kCol)::value ? G : G + 1;
+            const Taps<C, n> top = ld_taps<T, C, n>(vw, plane);
+            Taps<C, n> bot;
+            if constexpr (!decltype(kFlat)::value) bot = ld_taps<T, C, n>(vw + row, plane);
 #pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const T* __restrict__ vs = vt + (uint32_t)(s * C + c) * vstride;
-                float tv, val;
-                if (col) {
-                    tv = ld(vs + o);
-                    val = flat ? tv : fmaf(fy, ld(vs + o + Wp) - tv, tv);
+            for (int g = 0; g < G; ++g) {
+                float sq = 0.0f, dist = 0.0f;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    float val = top.e[c][g];
+                    if constexpr (!decltype(kCol)::value)
+                        val = fmaf(fx, top.e[c][g + 1] - top.e[c][g], top.e[c][g]);
+                    if constexpr (!decltype(kFlat)::value) {
+                        float bv = bot.e[c][g];
+                        if constexpr (!decltype(kCol)::value)
+                            bv = fmaf(fx, bot.e[c][g + 1] - bot.e[c][g], bot.e[c][g]);
+                        val = fmaf(fy, bv - val, val);
+                    }
+                    const float dl = ref.e[c][g] - val;
+                    dist = fabsf(dl);
+                    sq = c == 0 ? dl * dl : fmaf(dl, dl, sq);   // colour: l2 norm
+                }
+                if constexpr (C == 1) {
+                    acc[g] = acc[g] + dist;
+                } else if constexpr (!decltype(kRoot)::value) {
+                    acc[g] = acc[g] + sqrtf(sq);
                 } else {
-                    const Pair<T> top = ld_pair(vs + o);
-                    tv = fmaf(fx, top.hi - top.lo, top.lo);
-                    val = tv;
-                    if (!flat) {
-                        const Pair<T> bot = ld_pair(vs + o + Wp);
-                        const float bv = fmaf(fx, bot.hi - bot.lo, bot.lo);
-                        val = fmaf(fy, bv - tv, tv);
+                    acc[g] = acc[g] + root(sq);
+                    if constexpr (sizeof(T) == 4) {
+                        lim[0] = min(lim[0], __float_as_uint(sq) - 1u);
+                        lim[1] = max(lim[1], __float_as_uint(sq));
                     }
                 }
-                const float dl = ref[c] - val;
-                dist = fabsf(dl);
-                sq = c == 0 ? dl * dl : fmaf(dl, dl, sq);   // colour: l2 norm
             }
-            acc = acc + (C == 1 ? dist : sqrtf(sq));
         };
         // s ascending; the reference view itself adds exactly +0 and is skipped
-        auto view_row = [&](const T* __restrict__ vt, uint32_t rt, float fy, bool flat) {
-            for (int s = 0; s < sh; ++s) view(vt, rt, fy, s, flat, false);
-            if (!flat) view(vt, rt, fy, sh, false, true);
-            for (int s = sh + 1; s < S; ++s) view(vt, rt, fy, s, flat, false);
+        auto view_row = [&](const char* __restrict__ rt, float fy, auto flat) {
+            for (int s = 0; s < sh; ++s) view(rt, fy, s, flat, no);
+            if constexpr (!decltype(flat)::value) view(rt, fy, sh, no, yes);
+            for (int s = sh + 1; s < S; ++s) view(rt, fy, s, flat, no);
         };
         for (int t = 0; t < T_; ++t) {
             const float shy = (float)(th - t) * d;
             const float y0 = floorf(shy);
             const float fy = shy - y0;
-            // top tap row in padded coordinates; the bottom one follows it
-            const uint32_t rt = (uint32_t)(clampi(v + (int)y0, -1, H - 1) + kPadT) * Wp;
-            const T* __restrict__ vt = views + (size_t)t * S * C * vstride;
-            if (t == th) view_row(vt, rt, fy, true);
-            else view_row(vt, rt, fy, false);
-        }
-        return acc;
-    };
-
-    // Eq. (12) for the kGroup pixels (u + g, v) at one hypothesis d, with the
-    // arithmetic of cell() for each.  The shift of a view is the same for all of
-    // them, so pixel g's taps are pixel 0's moved by g elements: one load of
-    // kGroup + 1 elements per tap row serves the group (kGroup elements for the
-    // reference column of views, where only each pixel's left tap counts).
-    auto group = [&](int u, int v, float d, float (&acc)[kGroup]) {
-        const float* __restrict__ fv = (const float*)views;
-        const float* __restrict__ rp =
-            fv + ((size_t)th * S + sh) * vstride + (uint32_t)(v + kPadT) * Wp + u + kPadL;
-        float ref[kGroup];
-#pragma unroll
-        for (int g = 0; g < kGroup; ++g) {
-            ref[g] = rp[g];
-            acc[g] = 0.0f;
-        }
-        auto view = [&](const float* __restrict__ vt, uint32_t rt, float fy, int s, bool flat,
-                        bool col) {
-            const float shx = (float)(sh - s) * d;
-            const float x0 = floorf(shx);
-            const float fx = shx - x0;
-            const float* __restrict__ pv = vt + (uint32_t)s * vstride + rt +
-                                           (uint32_t)(clampi(u + (int)x0, -kPadL, W - 1) + kPadL);
-            float val[kGroup];
-            if (col) {                            // fx = 0: the left taps only
-                float top[kGroup];
-                __builtin_memcpy(&top, pv, sizeof(top));
-#pragma unroll
-                for (int g = 0; g < kGroup; ++g) val[g] = top[g];
-                if (!flat) {
-                    float bot[kGroup];
-                    __builtin_memcpy(&bot, pv + Wp, sizeof(bot));
-#pragma unroll
-                    for (int g = 0; g < kGroup; ++g) val[g] = fmaf(fy, bot[g] - val[g], val[g]);
-                }
-            } else {
-                const Row top = ld_row(pv);
-#pragma unroll
-                for (int g = 0; g < kGroup; ++g)
-                    val[g] = fmaf(fx, top.e[g + 1] - top.e[g], top.e[g]);
-                if (!flat) {
-                    const Row bot = ld_row(pv + Wp);
-#pragma unroll
-                    for (int g = 0; g < kGroup; ++g) {
-                        const float bv = fmaf(fx, bot.e[g + 1] - bot.e[g], bot.e[g]);
-                        val[g] = fmaf(fy, bv - val[g], val[g]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < kGroup; ++g) acc[g] = acc[g] + fabsf(ref[g] - val[g]);
-        };
-        auto view_row = [&](const float* __restrict__ vt, uint32_t rt, float fy, bool flat) {
-            for (int s = 0; s < sh; ++s) view(vt, rt, fy, s, flat, false);
-            if (!flat) view(vt, rt, fy, sh, false, true);
-            for (int s = sh + 1; s < S; ++s) view(vt, rt, fy, s, flat, false);
-        };
-        for (int t = 0; t < T_; ++t) {
-            const float shy = (float)(th - t) * d;
-            const float y0 = floorf(shy);
-            const float fy = shy - y0;
-            const uint32_t rt = (uint32_t)(clampi(v + (int)y0, -1, H - 1) + kPadT) * Wp;
-            const float* __restrict__ vt = fv + (size_t)t * S * vstride;
-            if (t == th) view_row(vt, rt, fy, true);
-            else view_row(vt, rt, fy, false);
+            // the top tap row, from its element at x = 0; the bottom one follows it
+            const char* __restrict__ rt =
+                view_at(t, 0) + (uint32_t)(clampi(v + (int)y0, -1, H - 1) + kPadT) * row;
+            if (t == th) view_row(rt, fy, yes);
+            else view_row(rt, fy, no);
         }
     };
 
@@ -350,104 +325,124 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, int64_t* 
         const int64_t c0 = slice * kChunk;
         const int64_t c1 = min(c0 + kChunk, total);
         if constexpr (Walk) __syncthreads();      // LDS of the previous slice is read
-        if (threadIdx.x == 0) {
-            int x = 0, y = HW;                    // off[x] <= c0 < off[y]
-            while (y - x > 1) {
-                const int mid = (x + y) >> 1;
-                if (off[mid] <= c0) x = mid; else y = mid;
-            }
-            s_p[0] = x;
-            s_p[1] = min(kChunk, HW - x);
+        // the slice's first pixel, off[p0] <= c0 < off[p0 + 1]: every wave searches by
+        // itself, 64 pixels at a time (four rounds for 2^24 of them; a binary search is
+        // 24 loads one after the other, which took most of a slice's time with few views)
+        int p0 = 0, n = HW;                       // p0 <= the pixel < p0 + n
+        while (n > 1) {
+            const int step = (n + 63) / 64;
+            const int at = p0 + (int)(threadIdx.x & 63) * step;
+            const bool below = at < p0 + n && off[at] <= c0;      // the first lane is
+            const int hit = max(__popcll(__builtin_amdgcn_ballot_w64(below)) - 1, 0);
+            const int end = p0 + n;
+            p0 += hit * step;
+            n = min(step, end - p0);
         }
-        __syncthreads();
-        const int p0 = s_p[0], npx = s_p[1];
+        const int npx = min(kChunk, HW - p0), len = (int)(c1 - c0);
+        const int v0 = p0 / W, u0 = p0 - v0 * W;  // wave-uniform
         for (int i = threadIdx.x; i <= npx; i += kThreads) {
-            s_off[i] = off[p0 + i];
-            if (i < npx) s_lo[i] = lo[p0 + i];
+            sl.rel[i] = (int)(off[p0 + i] - c0);
+            if (i < npx) sl.lo[i] = lo[p0 + i];
+        }
+        if (threadIdx.x == 0) sl.np = 0;
+        __syncthreads();
+        // pixels that own cells of the slice: up to the last one that starts in it
+        for (int i = threadIdx.x; i < npx; i += kThreads)
+            if (sl.rel[i] < len && (i + 1 == npx || sl.rel[i + 1] >= len)) atomicMax(&sl.np, i + 1);
+        __syncthreads();
+        const int np = sl.np;
+
+        // Groups: a pixel at u = 0 mod G (or the slice's first pixel) with the following
+        // pixels of its row up to the next such u that are in the slice.  A group's
+        // items are the hypotheses k of the hull of its pixels' slice cells; an item
+        // computes the cells (p + g, k) of the group that exist.  The slice cells of pixel
+        // i are [max(rel[i], 0), min(rel[i + 1], len)), cell c is hypothesis
+        // lo[i] + c - rel[i]; a pixel whose range is empty -- possible only for bounds
+        // given with hi < lo -- adds nothing.
+        uint32_t cnt[CPT], rec[CPT], uv[CPT], own = 0;
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) {
+            const int i = (int)threadIdx.x * CPT + e;     // consecutive pixels per thread
+            cnt[e] = 0;
+            if (i >= np) continue;
+            int u = u0 + i, v = v0;
+            if (u >= W) {
+                v += u / W;
+                u = u % W;
+            }
+            if (i != 0 && u % G != 0) continue;
+            const int n = min(min(G - u % G, np - i), W - u);
+            int kl = INT_MAX, kh = INT_MIN;
+            for (int g = 0; g < n; ++g) {
+                const int r = sl.rel[i + g], f = max(r, 0), t = min(sl.rel[i + g + 1], len);
+                if (f >= t) continue;
+                const int l = sl.lo[i + g] - r;
+                kl = min(kl, l + f);
+                kh = max(kh, l + t - 1);
+            }
+            kl = max(kl, 0);                      // ranges outside [0, N) add nothing there
+            kh = min(kh, N - 1);
+            if (kl > kh) continue;
+            cnt[e] = (uint32_t)(kh - kl + 1);
+            rec[e] = (uint32_t)i | (uint32_t)n << 12 | (uint32_t)kl << 16;
+            uv[e] = (uint32_t)u | (uint32_t)v << 16;
+            own += 1u << 20 | cnt[e];             // at most 2,048 groups of 256 items
+        }
+        uint32_t total_groups;
+        uint32_t at = block_prefix(own, sl.wave, &total_groups);
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) {
+            if (cnt[e] == 0) continue;
+            sl.pre[at >> 20] = at & 0xFFFFFu;
+            sl.rec[at >> 20] = rec[e];
+            sl.uv[at >> 20] = uv[e];
+            at += 1u << 20 | cnt[e];
         }
         __syncthreads();
-        int np;                                   // pixels that own cells of the slice
-        {
-            int x = 0, y = npx;                   // largest i with s_off[i] <= c1 - 1
+        const int ngroups = (int)(total_groups >> 20), nitems = (int)(total_groups & 0xFFFFFu);
+        for (int j = threadIdx.x; j < nitems; j += kThreads) {
+            int x = 0, y = ngroups;               // largest x with pre[x] <= j
             while (y - x > 1) {
                 const int mid = (x + y) >> 1;
-                if (s_off[mid] <= c1 - 1) x = mid; else y = mid;
+                if ((int)sl.pre[mid] <= j) x = mid; else y = mid;
             }
-            np = x + 1;
-        }
-
-        if constexpr (kPairs) {
-            // Groups of the slice's pixels: a pixel at u = 0 mod kGroup (or the
-            // slice's first pixel) with the following pixels of its row up to the
-            // next such u that are in the slice.  A group's items are the
-            // hypotheses k of the hull of its pixels' slice cells; an item
-            // computes the cells (p + g, k) of the group that exist.
-            auto first = [&](int i) { return max(s_off[i], c0); };       // slice cells of
-            auto last = [&](int i) { return min(s_off[i + 1], c1) - 1; }; // pixel i
-            auto kfirst = [&](int i) { return s_lo[i] + (int)(first(i) - s_off[i]); };
-            auto klast = [&](int i) { return s_lo[i] + (int)(last(i) - s_off[i]); };
-            auto ucol = [&](int i) { return (p0 + i) % W; };
-            auto leads = [&](int i) { return i == 0 || ucol(i) % kGroup == 0; };
-            auto members = [&](int i) {           // pixels of the group led by pixel i
-                const int u = ucol(i);
-                return min(min(kGroup - u % kGroup, np - i), W - u);
-            };
-            // hull [kl, kh] of the group led by pixel i (a pixel whose range is
-            // empty -- possible only for bounds given with hi < lo -- adds nothing)
-            auto hull = [&](int i, int n, int& kl, int& kh) {
-                kl = INT_MAX;
-                kh = INT_MIN;
-                for (int g = 0; g < n; ++g)
-                    if (first(i + g) <= last(i + g)) {
-                        kl = min(kl, kfirst(i + g));
-                        kh = max(kh, klast(i + g));
-                    }
-                return kl <= kh;
-            };
-            auto count = [&](int i) {
-                int kl, kh;
-                return leads(i) && hull(i, members(i), kl, kh) ? kh - kl + 1 : 0;
-            };
-            block_prefix(np, count, s_pre, s_tmp);
-            const int nitems = s_pre[np];
-            for (int j = threadIdx.x; j < nitems; j += kThreads) {
-                int x = 0, y = np;                // largest i with s_pre[i] <= j
-                while (y - x > 1) {
-                    const int mid = (x + y) >> 1;
-                    if (s_pre[mid] <= j) x = mid; else y = mid;
-                }
-                const int i = x;
-                const int n = members(i);
-                int kl, kh;
-                hull(i, n, kl, kh);
-                const int k = kl + (j - s_pre[i]);
-                bool has[kGroup], any = false;
+            const uint32_t gr = sl.rec[x], at = sl.uv[x];
+            const int i = (int)(gr & 0xFFFu), n = (int)(gr >> 12 & 15u);
+            const int k = (int)(gr >> 16) + (j - (int)sl.pre[x]);
+            const int u = (int)(at & 0xFFFFu), v = (int)(at >> 16);
+            int cell[G];                          // of the slice, or -1
+            bool any = false;
 #pragma unroll
-                for (int g = 0; g < kGroup; ++g) {
-                    has[g] = g < n && k >= kfirst(i + g) && k <= klast(i + g) &&
-                             (unsigned)k < (unsigned)N;
-                    any |= has[g];
+            for (int g = 0; g < G; ++g) {
+                cell[g] = -1;
+                if (g < n) {
+                    const int r = sl.rel[i + g], c = r + k - sl.lo[i + g];
+                    if (c >= max(r, 0) && c < min(sl.rel[i + g + 1], len)) cell[g] = c;
                 }
-                if (!any) continue;               // a gap of the hull, or a range
-                const int p = p0 + i;             // outside [0, N)
-                const int v = p / W, u = p - v * W;
-                float acc[kGroup];
-                group(u, v, a.hyp[k], acc);
+                any |= cell[g] >= 0;
+            }
+            if (!any) continue;                   // a gap of the hull
+            const float d = a.hyp[k];
+            float acc[G];
+            uint32_t lim[2] = {~0u, 0u};
+            if constexpr (C == 1) {
+                group(u, v, d, acc, lim, std::false_type());
+            } else if constexpr (sizeof(T) == 1) {
+                // 8-bit samples: a bilinear sum that is not its reference differs from
+                // it by at least 2^-24, or where that is 0 by a product of two
+                // fractions, each 0 or at least 2^-24 for such shifts
+                if (d == 0.0f || fabsf(d) >= 0x1p-24f)
+                    group(u, v, d, acc, lim, std::true_type());
+                else
+                    group(u, v, d, acc, lim, std::false_type());
+            } else {
+                group(u, v, d, acc, lim, std::true_type());
+                if (lim[0] < __float_as_uint(kRootMin) - 1u || lim[1] > __float_as_uint(kRootMax))
+                    group(u, v, d, acc, lim, std::false_type());
+            }
 #pragma unroll
-                for (int g = 0; g < kGroup; ++g)
-                    if (has[g]) store(s_off[i + g] + (k - s_lo[i + g]), acc[g]);
-            }
-        } else {
-            for (int r = 0; r < CPT; ++r) {
-                const int64_t c = c0 + threadIdx.x + (int64_t)r * kThreads;
-                if (c >= c1) break;
-                const int i = find_pixel(s_off, np, c);
-                const int p = p0 + i;
-                const int v = p / W, u = p - v * W;
-                const int k = s_lo[i] + (int)(c - s_off[i]);
-                if ((unsigned)k >= (unsigned)N) continue;      // only for ranges outside [0, N)
-                store(c, cell(u, v, a.hyp[k]));
-            }
+            for (int g = 0; g < G; ++g)
+                if (cell[g] >= 0) store(c0 + cell[g], acc[g]);
         }
         if constexpr (!Walk) break;               // one slice per workgroup
     }
@@ -455,15 +450,10 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, int64_t* 
 
 template <class Src, typename T, int CPT, bool Walk, int C>
 __global__ __launch_bounds__(kThreads) void cost_l2_kernel(Src src) {
-    constexpr bool kPairs = sizeof(T) == 4 && C == 1;
-    __shared__ int64_t s_off[kThreads * CPT + 1];
-    __shared__ int s_lo[kThreads * CPT];
-    __shared__ int s_p[2];
-    __shared__ int s_pre[kPairs ? kThreads * CPT + 1 : 1];
-    __shared__ int s_tmp[kPairs ? kThreads : 1];
+    __shared__ SliceLds<CPT> sl;
     uint32_t b;
     const L2Args& a = member(src, blockIdx.x, b);
-    l2_slices<T, CPT, Walk, C>(a, b, s_off, s_lo, s_p, s_pre, s_tmp);
+    l2_slices<T, CPT, Walk, C>(a, b, sl);
 }
 
 // ---------------------------------------------------------------------------
@@ -555,8 +545,8 @@ hipError_t l2_walk(Runner& r, const std::vector<L2Args>& args,
 hipError_t stage_cost_inputs(Runner& r, const Jobs& jobs) {
     // l2 cost: the edge-replicated copy of every view plane; Eq. (15) cost: the
     // Census strings of every view
-    std::vector<PadArgs> pads[2];
-    std::vector<uint32_t> pad_blocks[2];
+    std::vector<PadArgs> pads[3];                  // u8, f32, u8 colour
+    std::vector<uint32_t> pad_blocks[3];
     Jobs census_jobs;
     for (const Job* j : jobs) {
         if (j->prm.cost_kind != LF_COST_L2) {
@@ -569,19 +559,25 @@ hipError_t stage_cost_inputs(Runner& r, const Jobs& jobs) {
         pa.H = j->H;
         pa.W = j->W;
         pa.pitch = j->pitch;
-        pads[j->dtype == LF_U8 ? 0 : 1].push_back(pa);
-        pad_blocks[j->dtype == LF_U8 ? 0 : 1].push_back(
-            (uint32_t)((j->H + kPadH + kPadRows - 1) / kPadRows) * j->S * j->T * j->C);
+        const int k = j->dtype != LF_U8 ? 1 : j->C == 3 ? 2 : 0;
+        pads[k].push_back(pa);
+        pad_blocks[k].push_back((uint32_t)((j->H + kPadH + kPadRows - 1) / kPadRows) * j->S *
+                                j->T * (k == 2 ? 1 : j->C));
     }
     hipError_t e = hipSuccess;
     if (!pads[0].empty() &&
-        (e = launch(r, kStCostInputs, pad_views_kernel<Single<PadArgs>, uint8_t>,
-                    pad_views_kernel<Group<PadArgs>, uint8_t>, pads[0], pad_blocks[0],
+        (e = launch(r, kStCostInputs, pad_views_kernel<Single<PadArgs>, uint8_t, false>,
+                    pad_views_kernel<Group<PadArgs>, uint8_t, false>, pads[0], pad_blocks[0],
+                    kThreads)) != hipSuccess)
+        return e;
+    if (!pads[2].empty() &&
+        (e = launch(r, kStCostInputs, pad_views_kernel<Single<PadArgs>, uint8_t, true>,
+                    pad_views_kernel<Group<PadArgs>, uint8_t, true>, pads[2], pad_blocks[2],
                     kThreads)) != hipSuccess)
         return e;
     if (!pads[1].empty() &&
-        (e = launch(r, kStCostInputs, pad_views_kernel<Single<PadArgs>, float>,
-                    pad_views_kernel<Group<PadArgs>, float>, pads[1], pad_blocks[1],
+        (e = launch(r, kStCostInputs, pad_views_kernel<Single<PadArgs>, float, false>,
+                    pad_views_kernel<Group<PadArgs>, float, false>, pads[1], pad_blocks[1],
                     kThreads)) != hipSuccess)
         return e;
     if (!census_jobs.empty()) e = stage_census(r, census_jobs, true);
