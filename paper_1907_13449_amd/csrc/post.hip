@@ -1,7 +1,7 @@
 // Per-pixel stages around the two SGM passes (Sec. 3.4-3.6): fusion of the
 // intermediate maps, median hole filling, Sobel edge exclusion and the borders
 // of Eq. (11), the prefix sum that indexes the bounded volume, WTA with the
-// parabola sub-pixel refinement, and the 3x3 median.  All HBM-light: one thread
+// parabola sub-pixel refinement, and the 3x3 median.  All HBM-light: mostly one thread
 // per pixel, coalesced along rows.
 #include "lf_internal.h"
 
@@ -383,32 +383,122 @@ struct WtaArgs {
     int HW, N;
 };
 
+// What bounds the search is the loads of the costs.  A thread per pixel has one load
+// instruction per hypothesis, each touching a line or more per lane, and a wave waits for
+// its widest pixel (79 us of 37 M 32-bit costs, 1080 x 1920 pixels, an eighth of which
+// have 96 hypotheses; 90 us of 512^2 x 100).  So a lane loads a narrow pixel's costs 8 at
+// a time, and wide pixels are left to 16 lanes each, which load neighbouring costs.
+// Now 38 and 21 us; the bytes take 38 and 21 us at the rate of a large copy.
+constexpr int kNarrow = 16;        // hypotheses of the widest narrow pixel: two rounds
+
+// 8 consecutive costs.
+__device__ __forceinline__ void ld8(const uint32_t* c, uint32_t (&x)[8]) {
+    __builtin_memcpy(x, c, 16);
+    __builtin_memcpy(x + 4, c + 4, 16);
+}
+__device__ __forceinline__ void ld8(const uint16_t* c, uint32_t (&x)[8]) {
+    uint32_t w[4];
+    __builtin_memcpy(w, c, 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        x[2 * i] = w[i] & 0xFFFF;
+        x[2 * i + 1] = w[i] >> 16;
+    }
+}
+
+// Smallest value of 16 lanes, in each of them.
+__device__ __forceinline__ uint32_t row_least(uint32_t x) {
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true));
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, true));
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xF, 0xF, true));
+    return min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xF, 0xF, true));
+}
+
+// A wave's wide pixels: where their costs start, how many there are and the lane that
+// has the pixel; and the winners by that lane.
+struct WideLds {
+    int64_t off[64];
+    int n[64];                     // hypotheses | lane << 16
+    int best[64];
+};
+
 template <typename SumT>
-__device__ __forceinline__ void wta_pixel(const WtaArgs& a, int p) {
+__device__ __forceinline__ void wta_pixels(const WtaArgs& a, int p, WideLds& wl) {
+    const int lane = threadIdx.x & 63;
+    const int pc = min(p, a.HW - 1);
+    const SumT* __restrict__ csum = (const SumT*)a.csum;
+    const int64_t o = a.off[pc];
     // bounds outside the documented 0 <= lo <= hi < N are clamped into it, so no
     // hypothesis outside [0, N) is read (the result is then unspecified)
-    const int l = clampi(a.lo[p], 0, a.N - 1), h = clampi(a.hi[p], l, a.N - 1);
-    const SumT* c = (const SumT*)a.csum + a.off[p] - l;     // c[k] for k in [l, h]
-    const float* hyp = a.hyp;
-    // in increasing k, strict <, so the lowest index wins ties; eight loads in
-    // flight per round (indices past h re-read c[h] and are not compared)
-    int best = l;
-    uint32_t bv = c[l];
-    for (int k0 = l + 1; k0 <= h; k0 += 8) {
-        uint32_t x[8];
+    const int l = clampi(a.lo[pc], 0, a.N - 1), h = clampi(a.hi[pc], l, a.N - 1);
+    const int n = h - l + 1;
+    const SumT* __restrict__ c = csum + o;                  // c[i] is hypothesis l + i
+    // in increasing order, strict <, so the lowest index wins ties
+    int best = 0;
+    uint32_t bv = 0;
+    const bool wide = p < a.HW && n > kNarrow;
+    if (!wide) {
+        const int64_t left = a.off[a.HW] - o;               // costs from here to the end
+        for (int i0 = 0; i0 < n; i0 += 8) {
+            uint32_t x[8];
+            if (__builtin_expect(i0 + 8 <= left, 1)) {
+                ld8(c + i0, x);
+            } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = c[min(k0 + i, h)];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (k0 + i <= h && x[i] < bv) {
-                bv = x[i];
-                best = k0 + i;
+                for (int i = 0; i < 8; ++i) x[i] = c[min(i0 + i, n - 1)];
             }
+            if (i0 == 0) bv = x[0];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (i0 + i < n && x[i] < bv) {
+                    bv = x[i];
+                    best = i0 + i;
+                }
+        }
     }
-    a.d_index[p] = (int16_t)best;
+    const uint64_t wides = __builtin_amdgcn_ballot_w64(wide);
+    if (wides != 0) {                                       // uniform
+        if (wide) {
+            const int at = __popcll(wides & ((1ull << lane) - 1));
+            wl.off[at] = o;
+            wl.n[at] = n | lane << 16;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int count = __popcll(wides), sub = lane & 15;
+        for (int r = 0; r < count; r += 4) {
+            const int i = min(r + (lane >> 4), count - 1);  // the last one again: the same
+            const int packed = wl.n[i], m = packed & 0xFFFF;
+            const SumT* __restrict__ w = csum + wl.off[i];
+            uint32_t least = 0;
+            int at = 0;
+            for (int k0 = sub; k0 < m; k0 += 128) {
+                uint32_t x[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) x[j] = w[min(k0 + 16 * j, m - 1)];
+                if (k0 == sub) least = x[0], at = sub;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (k0 + 16 * j < m && x[j] < least) {
+                        least = x[j];
+                        at = k0 + 16 * j;
+                    }
+            }
+            const uint32_t all = row_least(least);
+            const uint32_t first = row_least(least == all ? (uint32_t)at : ~0u);
+            if (sub == 0) wl.best[packed >> 16] = (int)first;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (wide) {
+            best = wl.best[lane];
+            bv = c[best];
+        }
+    }
+    if (p >= a.HW) return;
+    a.d_index[p] = (int16_t)(l + best);
+    const float* __restrict__ hyp = (const float*)a.hyp + l;
     float d = hyp[best];
-    if (best - 1 >= l && best + 1 <= h && h - l >= 4) {
-        const int64_t cm = c[best - 1], c0 = c[best], cp = c[best + 1];
+    if (best >= 1 && best + 1 < n && n >= 5) {
+        const int64_t cm = c[best - 1], c0 = bv, cp = c[best + 1];
         const float o = (float)(cm - cp) / (2.0f * (float)(cm + cp - 2 * c0));
         d = o >= 0.0f ? fmaf(o, hyp[best + 1] - hyp[best], hyp[best])
                       : fmaf(o, hyp[best] - hyp[best - 1], hyp[best]);
@@ -418,11 +508,11 @@ __device__ __forceinline__ void wta_pixel(const WtaArgs& a, int p) {
 
 template <class Src, typename SumT>
 __global__ __launch_bounds__(kThreads) void wta_subpixel_kernel(Src src) {
+    __shared__ WideLds wl[kThreads / 64];
     for (uint32_t vb = blockIdx.x; vb < src.total; vb += gridDim.x) {
         uint32_t b;
         const WtaArgs& a = member(src, vb, b);
-        const int p = (int)b * kThreads + threadIdx.x;
-        if (p < a.HW) wta_pixel<SumT>(a, p);
+        wta_pixels<SumT>(a, (int)b * kThreads + threadIdx.x, wl[threadIdx.x >> 6]);
     }
 }
 
@@ -433,16 +523,32 @@ struct MedianArgs {
     int H, W;
 };
 
-__device__ __forceinline__ void median_pixel(const MedianArgs& a, int p) {
-    const int H = a.H, W = a.W;
-    const int v = p / W, u = p - v * W;
+// A thread takes kMedianRows pixels of a column, whose windows share rows: a row's three
+// values are ordered once, and the median of nine is the median of the largest of the
+// rows' least, the median of their medians and the least of their largest.  Bound by
+// its loads, 18 for four pixels (1080 x 1920: 6 us; by ranks, a pixel per thread, 46 us).
+constexpr int kMedianRows = 4;
+
+// Order-preserving integers of the floats other than NaN (-0 before +0), and back.
+__device__ __forceinline__ int ordered(float x) {
+    const int i = __float_as_int(x);
+    return i ^ (i >> 31 & 0x7FFFFFFF);
+}
+__device__ __forceinline__ float unordered(int i) {
+    return __int_as_float(i ^ (i >> 31 & 0x7FFFFFFF));
+}
+__device__ __forceinline__ int mid3(int x, int y, int z) {
+    return max(min(x, y), min(max(x, y), z));
+}
+
+// The median of a window with NaN: by ranks, a NaN having none (the centre if no value
+// has at most 4 values below it and at least 5 at or below).
+__device__ __forceinline__ float median_by_rank(const MedianArgs& a, int v, int u) {
     float w[9];
-    int n = 0;
-    for (int i = -1; i <= 1; ++i) {
-        const int y = clampi(v + i, 0, H - 1);
-        for (int j = -1; j <= 1; ++j) w[n++] = a.in[(size_t)y * W + clampi(u + j, 0, W - 1)];
-    }
-    // rank selection: the median has at most 4 values below it and at least 5 at or below
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+        w[i] = a.in[(size_t)clampi(v + i / 3 - 1, 0, a.H - 1) * a.W +
+                    clampi(u + i % 3 - 1, 0, a.W - 1)];
     float med = w[4];
 #pragma unroll
     for (int x = 0; x < 9; ++x) {
@@ -454,7 +560,46 @@ __device__ __forceinline__ void median_pixel(const MedianArgs& a, int p) {
         }
         if (below <= 4 && 4 < atmost) med = w[x];
     }
-    a.out[p] = med;
+    return med;
+}
+
+__device__ __forceinline__ void median_pixels(const MedianArgs& a, int i) {
+    const int H = a.H, W = a.W;
+    const int q = i / W, u = i - q * W, v0 = q * kMedianRows;
+    if (v0 >= H) return;
+    const float* __restrict__ in = a.in;
+    const int um = max(u - 1, 0), up = min(u + 1, W - 1);
+    float x[kMedianRows + 2][3];
+#pragma unroll
+    for (int r = 0; r < kMedianRows + 2; ++r) {
+        const float* __restrict__ row = in + (size_t)clampi(v0 + r - 1, 0, H - 1) * W;
+        x[r][0] = row[um];
+        x[r][1] = row[u];
+        x[r][2] = row[up];
+    }
+    float any = 0.0f;                             // NaN if one of the values is
+    int lo[kMedianRows + 2], mid[kMedianRows + 2], hi[kMedianRows + 2];
+#pragma unroll
+    for (int r = 0; r < kMedianRows + 2; ++r) {
+        any += x[r][0] + x[r][1] + x[r][2];
+        const int p = ordered(x[r][0]), c = ordered(x[r][1]), n = ordered(x[r][2]);
+        lo[r] = min(min(p, c), n);
+        mid[r] = mid3(p, c, n);
+        hi[r] = max(max(p, c), n);
+    }
+    float* __restrict__ out = a.out + (size_t)v0 * W + u;
+    if (__builtin_expect(any != any, 0)) {
+#pragma unroll 1
+        for (int r = 0; r < min(kMedianRows, H - v0); ++r)
+            out[(size_t)r * W] = median_by_rank(a, v0 + r, u);
+        return;
+    }
+#pragma unroll
+    for (int r = 0; r < kMedianRows; ++r)
+        if (v0 + r < H)
+            out[(size_t)r * W] = unordered(mid3(max(max(lo[r], lo[r + 1]), lo[r + 2]),
+                                                mid3(mid[r], mid[r + 1], mid[r + 2]),
+                                                min(min(hi[r], hi[r + 1]), hi[r + 2])));
 }
 
 template <class Src>
@@ -462,8 +607,7 @@ __global__ __launch_bounds__(kThreads) void median3_kernel(Src src) {
     for (uint32_t vb = blockIdx.x; vb < src.total; vb += gridDim.x) {
         uint32_t b;
         const MedianArgs& a = member(src, vb, b);
-        const int p = (int)b * kThreads + threadIdx.x;
-        if (p < a.H * a.W) median_pixel(a, p);
+        median_pixels(a, (int)b * kThreads + threadIdx.x);
     }
 }
 
@@ -619,7 +763,8 @@ hipError_t stage_wta(Runner& r, const Jobs& jobs) {
         wta_blocks[sb].push_back(blocks_for(HW));
         if (median) {
             med.push_back(MedianArgs{j->pre_median, j->disparity, j->H, j->W});
-            med_blocks.push_back(blocks_for(HW));
+            med_blocks.push_back(
+                blocks_for((int64_t)((j->H + kMedianRows - 1) / kMedianRows) * j->W));
         }
     }
     hipError_t e = hipSuccess;
