@@ -18,17 +18,23 @@
 namespace lf {
 namespace {
 
-constexpr int kPix = 64;        // pixels per workgroup (Census kind)
 constexpr int kThreads = 256;
 
-// Largest i with s_off[i] <= c (the pixel that owns cell c).
-__device__ __forceinline__ int find_pixel(const int64_t* s_off, int np, int64_t c) {
-    int a = 0, b = np;            // invariant: s_off[a] <= c < s_off[b]
-    while (b - a > 1) {
-        const int mid = (a + b) >> 1;
-        if (s_off[mid] <= c) a = mid; else b = mid;
+// The pixel that owns cell c0, off[p0] <= c0 < off[p0 + 1], of HW pixels: every wave
+// searches by itself, 64 pixels at a time (four rounds for 2^24 of them; a binary search
+// is 24 loads one after the other, which took most of a slice's time with few views).
+__device__ __forceinline__ int first_pixel(const int64_t* __restrict__ off, int HW, int64_t c0) {
+    int p0 = 0, n = HW;                       // p0 <= the pixel < p0 + n
+    while (n > 1) {
+        const int step = (n + 63) / 64;
+        const int at = p0 + (int)(threadIdx.x & 63) * step;
+        const bool below = at < p0 + n && off[at] <= c0;          // the first lane is
+        const int hit = max(__popcll(__builtin_amdgcn_ballot_w64(below)) - 1, 0);
+        const int end = p0 + n;
+        p0 += hit * step;
+        n = min(step, end - p0);
     }
-    return a;
+    return p0;
 }
 
 // ---------------------------------------------------------------------------
@@ -325,19 +331,7 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
         const int64_t c0 = slice * kChunk;
         const int64_t c1 = min(c0 + kChunk, total);
         if constexpr (Walk) __syncthreads();      // LDS of the previous slice is read
-        // the slice's first pixel, off[p0] <= c0 < off[p0 + 1]: every wave searches by
-        // itself, 64 pixels at a time (four rounds for 2^24 of them; a binary search is
-        // 24 loads one after the other, which took most of a slice's time with few views)
-        int p0 = 0, n = HW;                       // p0 <= the pixel < p0 + n
-        while (n > 1) {
-            const int step = (n + 63) / 64;
-            const int at = p0 + (int)(threadIdx.x & 63) * step;
-            const bool below = at < p0 + n && off[at] <= c0;      // the first lane is
-            const int hit = max(__popcll(__builtin_amdgcn_ballot_w64(below)) - 1, 0);
-            const int end = p0 + n;
-            p0 += hit * step;
-            n = min(step, end - p0);
-        }
+        const int p0 = first_pixel(off, HW, c0);
         const int npx = min(kChunk, HW - p0), len = (int)(c1 - c0);
         const int v0 = p0 / W, u0 = p0 - v0 * W;  // wave-uniform
         for (int i = threadIdx.x; i <= npx; i += kThreads) {
@@ -457,8 +451,10 @@ __global__ __launch_bounds__(kThreads) void cost_l2_kernel(Src src) {
 }
 
 // ---------------------------------------------------------------------------
-// Census kind, Eq. (15): 64 pixels per workgroup, their cells strided over the
-// threads.
+// Census kind, Eq. (15), in slices of cells like the l2 cost, a cell per thread and
+// round.  The gathers of the views' strings bound it, about 25 cycles of a CU for the 64
+// lanes of one.  A workgroup for 64 pixels, whatever their ranges, had stragglers (7x7x384^2,
+// N = 64: 261 us; 97 us in slices, 88 us with two views in flight, 93 us with four).
 struct CensusAllArgs {
     gptr<const uint64_t> census;   // [S*T][C][H*W]
     gptr<const float> hyp;
@@ -467,54 +463,83 @@ struct CensusAllArgs {
     gptr<uint16_t> cost;
     gptr<float> cost_f32;
     int64_t cap_cells;
-    int S, T, C, H, W, N;
+    int S, T, H, W, N;
     uint32_t cap;
 };
 
-template <class Src>
-__global__ __launch_bounds__(kThreads) void cost_census_all_kernel(Src src) {
-    __shared__ int64_t s_off[kPix + 1];
-    __shared__ int s_lo[kPix];
-    for (uint32_t vb = blockIdx.x; vb < src.total; vb += gridDim.x) {
-        uint32_t b;
-        const CensusAllArgs& a = member(src, vb, b);
-        const int S = a.S, T_ = a.T, H = a.H, W = a.W, N = a.N;
-        const int HW = H * W;
-        const int p0 = (int)b * kPix;
-        const int np = min(kPix, HW - p0);
-        __syncthreads();
-        for (int i = threadIdx.x; i <= np; i += kThreads) {
-            s_off[i] = a.off[p0 + i];
-            if (i < np) s_lo[i] = a.lo[p0 + i];
-        }
-        __syncthreads();
-        const int sh = (S - 1) / 2, th = (T_ - 1) / 2;
-        const int C = a.C;
-        const uint64_t* __restrict__ census = a.census;
-        const uint64_t* __restrict__ cref = census + ((size_t)th * S + sh) * C * HW;
-        for (int64_t c = s_off[0] + threadIdx.x; c < s_off[np]; c += kThreads) {
-            if (c >= a.cap_cells) break;
-            const int i = find_pixel(s_off, np, c);
-            const int p = p0 + i;
-            const int v = p / W, u = p - v * W;
-            const int k = s_lo[i] + (int)(c - s_off[i]);
-            if ((unsigned)k >= (unsigned)N) continue;
-            const float d = a.hyp[k];
-            uint32_t acc = 0;
-            for (int t = 0; t < T_; ++t) {
-                const int y = clampi(v + (int)rintf((float)(th - t) * d), 0, H - 1);
-                for (int s = 0; s < S; ++s) {
-                    const int x = clampi(u + (int)rintf((float)(sh - s) * d), 0, W - 1);
-                    for (int c = 0; c < C; ++c)             // colour: summed per channel
-                        acc += (uint32_t)__popcll(
-                            cref[(size_t)c * HW + p] ^
-                            census[(((size_t)t * S + s) * C + c) * HW + (size_t)y * W + x]);
-                }
-            }
-            a.cost[c] = (uint16_t)min(acc, a.cap);
-            if (a.cost_f32) a.cost_f32[c] = (float)acc;
-        }
+constexpr int kCensusChunk = 2 * kThreads;
+
+struct CensusLds {
+    int rel[kCensusChunk];         // a pixel's first cell, from the slice's first
+    int16_t lo[kCensusChunk];
+    int np;
+};
+
+template <int C>
+__device__ __forceinline__ void census_slice(const CensusAllArgs& a, uint32_t b, CensusLds& sl) {
+    const int S = a.S, T = a.T, H = a.H, W = a.W, N = a.N;
+    const int HW = H * W;
+    const int64_t* __restrict__ off = a.off;
+    const int64_t total = min(off[HW], a.cap_cells), c0 = (int64_t)b * kCensusChunk;
+    if (c0 >= total) return;                                // uniform
+    const int len = (int)min((int64_t)kCensusChunk, total - c0);
+    const int p0 = first_pixel(off, HW, c0);
+    const int npx = min(kCensusChunk, HW - p0);
+    const int v0 = p0 / W, u0 = p0 - v0 * W;
+    for (int i = threadIdx.x; i < npx; i += kThreads) {
+        sl.rel[i] = (int)(off[p0 + i] - c0);
+        sl.lo[i] = a.lo[p0 + i];
     }
+    if (threadIdx.x == 0) sl.np = 0;
+    __syncthreads();
+    // pixels that start before the slice's end
+    for (int i = threadIdx.x; i < npx; i += kThreads)
+        if (sl.rel[i] < len && (i + 1 == npx || sl.rel[i + 1] >= len)) atomicMax(&sl.np, i + 1);
+    __syncthreads();
+    const int np = sl.np;
+    const int sh = (S - 1) / 2, th = (T - 1) / 2;
+    const uint64_t* __restrict__ census = a.census;
+    const uint64_t* __restrict__ cref = census + ((size_t)th * S + sh) * C * HW;
+    for (int c = threadIdx.x; c < len; c += kThreads) {
+        int i = 0, end = np;                                // largest i with rel[i] <= c
+        while (end - i > 1) {
+            const int mid = (i + end) >> 1;
+            if (sl.rel[mid] <= c) i = mid; else end = mid;
+        }
+        const int k = sl.lo[i] + c - sl.rel[i];
+        if ((unsigned)k >= (unsigned)N) continue;
+        int v = v0, u = u0 + i;
+        if (u >= W) {
+            v += u / W;
+            u %= W;
+        }
+        const float d = a.hyp[k];
+        uint64_t ref[C];
+#pragma unroll
+        for (int ch = 0; ch < C; ++ch) ref[ch] = cref[(size_t)ch * HW + (p0 + i)];
+        uint32_t acc = 0;
+        for (int t = 0; t < T; ++t) {
+            const int y = clampi(v + (int)rintf((float)(th - t) * d), 0, H - 1);
+            const uint64_t* __restrict__ row = census + (size_t)t * S * C * HW + (size_t)y * W;
+#pragma unroll 2
+            for (int s = 0; s < S; ++s) {
+                const int x = clampi(u + (int)rintf((float)(sh - s) * d), 0, W - 1);
+#pragma unroll
+                for (int ch = 0; ch < C; ++ch)              // colour: summed per channel
+                    acc += (uint32_t)__popcll(ref[ch] ^ row[((size_t)s * C + ch) * HW + x]);
+            }
+        }
+        a.cost[c0 + c] = (uint16_t)min(acc, a.cap);
+        if (a.cost_f32) a.cost_f32[c0 + c] = (float)acc;
+    }
+}
+
+template <class Src, int C>
+__global__ __launch_bounds__(kThreads) void cost_census_kernel(Src src) {
+    __shared__ CensusLds sl;
+    uint32_t b;
+    const CensusAllArgs& a = member(src, blockIdx.x, b);
+    census_slice<C>(a, b, sl);
 }
 
 template <typename T, bool Walk, int C>
@@ -587,8 +612,8 @@ hipError_t stage_cost_inputs(Runner& r, const Jobs& jobs) {
 hipError_t stage_cost(Runner& r, const Jobs& jobs) {
     std::vector<L2Args> l2[2][2];                  // [u8/f32][gray/colour]
     std::vector<uint32_t> l2_blocks[2][2];
-    std::vector<CensusAllArgs> ca;
-    std::vector<uint32_t> ca_blocks;
+    std::vector<CensusAllArgs> ca[2];              // [gray/colour]
+    std::vector<uint32_t> ca_blocks[2];
     const int cpt = r.tune.cost_cpt == 2 || r.tune.cost_cpt == 8 ? r.tune.cost_cpt : 4;
     const int stride = std::max(1, r.tune.cost_stride);
     for (const Job* j : jobs) {
@@ -626,13 +651,13 @@ hipError_t stage_cost(Runner& r, const Jobs& jobs) {
             a.cap_cells = j->cap_cells;
             a.S = j->S;
             a.T = j->T;
-            a.C = j->C;
             a.H = j->H;
             a.W = j->W;
             a.N = j->N;
             a.cap = (uint32_t)j->cap;
-            ca.push_back(a);
-            ca_blocks.push_back((uint32_t)((HW + kPix - 1) / kPix));
+            const int col = j->C == 3 ? 1 : 0;
+            ca[col].push_back(a);
+            ca_blocks[col].push_back((uint32_t)((HW * j->N + kCensusChunk - 1) / kCensusChunk));
         }
     }
     hipError_t e = hipSuccess;
@@ -644,9 +669,14 @@ hipError_t stage_cost(Runner& r, const Jobs& jobs) {
         return e;
     if (!l2[1][1].empty() && (e = l2_walk<float, 3>(r, l2[1][1], l2_blocks[1][1])) != hipSuccess)
         return e;
-    if (!ca.empty())
-        e = launch(r, kStCost, cost_census_all_kernel<Single<CensusAllArgs>>,
-                   cost_census_all_kernel<Group<CensusAllArgs>>, ca, ca_blocks, kThreads);
+    if (!ca[0].empty() &&
+        (e = launch(r, kStCost, cost_census_kernel<Single<CensusAllArgs>, 1>,
+                    cost_census_kernel<Group<CensusAllArgs>, 1>, ca[0], ca_blocks[0],
+                    kThreads)) != hipSuccess)
+        return e;
+    if (!ca[1].empty())
+        e = launch(r, kStCost, cost_census_kernel<Single<CensusAllArgs>, 3>,
+                   cost_census_kernel<Group<CensusAllArgs>, 3>, ca[1], ca_blocks[1], kThreads);
     return e;
 }
 
