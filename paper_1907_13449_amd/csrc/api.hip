@@ -384,6 +384,7 @@ lf::Job depth_job(const lf_view_set* v, const float* hyp, int N, const lf_params
     j.cost = pl.cost;
     j.cost_f32 = nullptr;
     j.cap_cells = (int64_t)v->H * v->W * N;
+    j.full_range = prm->lambda < 0;
     j.sgm_ws = pl.sgm_ws;
     j.csum = pl.csum;
     j.d_index = d_index ? d_index : pl.d_index;

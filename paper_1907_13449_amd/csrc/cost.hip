@@ -451,6 +451,184 @@ __global__ __launch_bounds__(kThreads) void cost_l2_kernel(Src src) {
 }
 
 // ---------------------------------------------------------------------------
+// l2 cost where every pixel has the full range (a search without bounds, whose volume is
+// dense).  A lane has a block of R rows x G columns of pixels at one hypothesis: the
+// R + 1 tap rows of a view serve them all and are interpolated along the row once, and
+// neighbouring lanes load neighbouring taps.  The waves of a workgroup have the same
+// pixels at consecutive hypotheses, whose taps are in the same lines; they pass their
+// costs through LDS, to be written together (2-byte stores 2 N bytes apart took longer
+// than the sums where the views are few: 1x11x540x960 u8, N = 96, 257 us with them, 175
+// us with 4 hypotheses a store, 144 us with 8).  Bound by its arithmetic, about 8
+// instructions per cell and view, and nearly as much by the 16 bytes a lane loads per
+// row, which the cache delivers at 64 bytes a cycle; 2 or 4 hypotheses per lane leave
+// fewer waves to hide the loads' latency (667, 824 us against 568, 9x9x512^2 f32, N =
+// 100), as do more rows (4: 580 us; 2 rows load more, 613 us).  Faster than the slices
+// at every size tried (there 1141 us; 5x5x96^2 u8, N = 32: 17 us for 25; 3x3x64^2: 10 for
+// 16; colour 5x5x331x449, N = 77, f32 269 us for 424, u8 260 for 656).
+constexpr int kFullHyps = 8;
+template <typename T, int C>
+constexpr int kFullRows = C == 1 ? 3 : sizeof(T) == 1 ? 4 : 2;
+
+// Costs of the pixels u .. u + G-1 of the rows v0 .. v0 + R-1 at hypothesis d.
+template <typename T, int C, bool kRoot>
+__device__ __forceinline__ void full_item(const L2Args& a, int u, int v0, float d,
+                                          uint16_t (&cost)[kFullRows<T, C>][kGroupOf<T, C>]) {
+    constexpr int G = kGroupOf<T, C>, R = kFullRows<T, C>;
+    constexpr int CP = sizeof(T) == 1 && C == 3 ? 1 : C;
+    constexpr int kElem = sizeof(T) == 1 && C == 3 ? 4 : (int)sizeof(T);
+    const int S = a.S, T_ = a.T, H = a.H, W = a.W;
+    const int sh = (S - 1) / 2, th = (T_ - 1) / 2;
+    const int Wp = copy_width(H, W, kElem);
+    const uint32_t row = (uint32_t)Wp * kElem, plane = (uint32_t)(H + kPadH) * row;
+    const size_t vbytes = (size_t)plane * CP;
+    const char* __restrict__ views = (const char*)(const void*)a.views;
+
+    Taps<C, G> ref[R];
+    float acc[R][G];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        ref[r] = ld_taps<T, C, G>(views + ((size_t)th * S + sh) * vbytes +
+                                      (uint32_t)(min(v0 + r, H - 1) + kPadT) * row +
+                                      (uint32_t)(u + kPadL) * kElem, plane);
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[r][g] = 0.0f;
+    }
+    uint32_t lim_lo = ~0u, lim_hi = 0;            // as group()'s lim
+    for (int t = 0; t < T_; ++t) {
+        // the image rows v0 + y0 + 0..R, clamped: row i is pixel row i's top tap row and
+        // pixel row i-1's bottom one (the replicas are equal)
+        const float shy = (float)(th - t) * d;
+        const float y0 = floorf(shy);
+        const float fy = shy - y0;
+        uint32_t ro[R + 1];
+#pragma unroll
+        for (int r = 0; r <= R; ++r)
+            ro[r] = (uint32_t)(clampi(v0 + (int)y0 + r, 0, H - 1) + kPadT) * row;
+        const char* __restrict__ rt = views + (size_t)t * S * vbytes;
+        auto view = [&](int s, auto kFlat, auto kCol) {     // the cases of group()
+            const char* __restrict__ vw = rt + (size_t)(uint32_t)s * vbytes;
+            constexpr bool flat = decltype(kFlat)::value, col = decltype(kCol)::value;
+            const float shx = (float)(sh - s) * d;
+            const float x0 = floorf(shx);
+            const float fx = shx - x0;
+            const uint32_t xo = (uint32_t)(clampi(u + (int)x0, -kPadL, W - 1) + kPadL) * kElem;
+            float h[R + 1][C][G];
+#pragma unroll
+            for (int r = 0; r < (flat ? R : R + 1); ++r) {
+                constexpr int n = col ? G : G + 1;
+                const Taps<C, n> e = ld_taps<T, C, n>(vw + (ro[r] + xo), plane);
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        if constexpr (col) h[r][c][g] = e.e[c][g];
+                        else h[r][c][g] = fmaf(fx, e.e[c][g + 1] - e.e[c][g], e.e[c][g]);
+                    }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    float sq = 0.0f, dist = 0.0f;
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        float val = h[r][c][g];
+                        if constexpr (!flat) val = fmaf(fy, h[r + 1][c][g] - val, val);
+                        const float dl = ref[r].e[c][g] - val;
+                        dist = fabsf(dl);
+                        sq = c == 0 ? dl * dl : fmaf(dl, dl, sq);
+                    }
+                    if constexpr (C == 1) {
+                        acc[r][g] += dist;
+                    } else if constexpr (!kRoot) {
+                        acc[r][g] += sqrtf(sq);
+                    } else {
+                        acc[r][g] += root(sq);
+                        if constexpr (sizeof(T) == 4) {
+                            lim_lo = min(lim_lo, __float_as_uint(sq) - 1u);
+                            lim_hi = max(lim_hi, __float_as_uint(sq));
+                        }
+                    }
+                }
+        };
+        constexpr std::true_type yes;
+        constexpr std::false_type no;
+        if (t == th) {
+            for (int s = 0; s < S; ++s)
+                if (s != sh) view(s, yes, no);    // the reference view adds +0
+        } else {
+            for (int s = 0; s < sh; ++s) view(s, no, no);
+            view(sh, no, yes);
+            for (int s = sh + 1; s < S; ++s) view(s, no, no);
+        }
+    }
+    if constexpr (C == 3 && sizeof(T) == 4 && kRoot) {
+        if (lim_lo < __float_as_uint(kRootMin) - 1u || lim_hi > __float_as_uint(kRootMax)) {
+            full_item<T, C, false>(a, u, v0, d, cost);
+            return;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const float q = rintf(a.alpha * acc[r][g]);
+            cost[r][g] = (uint16_t)(q > a.cap ? a.cap : q);
+        }
+}
+
+template <typename T, int C>
+__host__ __device__ __forceinline__ uint32_t full_items(int H, int W) {
+    constexpr int G = kGroupOf<T, C>, R = kFullRows<T, C>;
+    return (uint32_t)((W + G - 1) / G) * (uint32_t)((H + R - 1) / R);
+}
+
+// Workgroup b: 64 items at kFullHyps hypotheses, one per wave; those of the same items
+// follow each other.
+template <class Src, typename T, int C>
+__global__ __launch_bounds__(64 * kFullHyps) void cost_l2_full_kernel(Src src) {
+    constexpr int G = kGroupOf<T, C>, R = kFullRows<T, C>;
+    __shared__ uint16_t s_cost[R][64 * G][kFullHyps];
+    uint32_t b;
+    const L2Args& a = member(src, blockIdx.x, b);
+    const uint32_t nk = (uint32_t)(a.N + kFullHyps - 1) / kFullHyps;
+    const uint32_t set = b / nk, wg = (uint32_t)((a.W + G - 1) / G);
+    const uint32_t items = full_items<T, C>(a.H, a.W);
+    const int k0 = (int)(b - set * nk) * kFullHyps;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (k0 + wave < a.N) {
+        const uint32_t item = min(set * 64 + lane, items - 1);
+        const int v = (int)(item / wg), u = (int)(item - (uint32_t)v * wg);
+        const float d = a.hyp[k0 + wave];
+        uint16_t cost[R][G];
+        // the root of 8-bit colour norms: as in l2_slices
+        if (C == 3 && sizeof(T) == 1 && d != 0.0f && !(fabsf(d) >= 0x1p-24f))
+            full_item<T, C, false>(a, u * G, v * R, d, cost);
+        else
+            full_item<T, C, C == 3>(a, u * G, v * R, d, cost);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int g = 0; g < G; ++g) s_cost[r][lane * G + g][wave] = cost[r][g];
+    }
+    __syncthreads();
+    const int n = min(kFullHyps, a.N - k0);
+    for (int j = threadIdx.x; j < R * 64 * G; j += 64 * kFullHyps) {
+        const int r = j / (64 * G), q = j - r * (64 * G);
+        const uint32_t item = set * 64 + (uint32_t)(q / G);
+        const int vi = (int)(item / wg);
+        const int v = vi * R + r, u = (int)(item - (uint32_t)vi * wg) * G + q % G;
+        if (item >= items || v >= a.H || u >= a.W) continue;
+        uint16_t* out = a.cost + ((int64_t)v * a.W + u) * a.N + k0;
+        if (n == kFullHyps) {
+            __builtin_memcpy(out, s_cost[r][q], 2 * kFullHyps);
+        } else {
+            for (int i = 0; i < n; ++i) out[i] = s_cost[r][q][i];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Census kind, Eq. (15), in slices of cells like the l2 cost, a cell per thread and
 // round.  The gathers of the views' strings bound it, about 25 cycles of a CU for the 64
 // lanes of one.  A workgroup for 64 pixels, whatever their ranges, had stragglers (7x7x384^2,
@@ -565,6 +743,18 @@ hipError_t l2_walk(Runner& r, const std::vector<L2Args>& args,
                                   : l2_variant<T, false, C>(r, args, blocks);
 }
 
+template <typename T, int C>
+hipError_t l2_full(Runner& r, const std::vector<L2Args>& args) {
+    std::vector<uint32_t> blocks;
+    for (const L2Args& a : args) {
+        blocks.push_back((full_items<T, C>(a.H, a.W) + 63) / 64 *
+                         ((uint32_t)(a.N + kFullHyps - 1) / kFullHyps));
+    }
+    return launch(r, kStCost, cost_l2_full_kernel<Single<L2Args>, T, C>,
+                  cost_l2_full_kernel<Group<L2Args>, T, C>, args, blocks,
+                  64 * kFullHyps);
+}
+
 }  // namespace
 
 hipError_t stage_cost_inputs(Runner& r, const Jobs& jobs) {
@@ -611,6 +801,7 @@ hipError_t stage_cost_inputs(Runner& r, const Jobs& jobs) {
 
 hipError_t stage_cost(Runner& r, const Jobs& jobs) {
     std::vector<L2Args> l2[2][2];                  // [u8/f32][gray/colour]
+    std::vector<L2Args> full[2][2];
     std::vector<uint32_t> l2_blocks[2][2];
     std::vector<CensusAllArgs> ca[2];              // [gray/colour]
     std::vector<uint32_t> ca_blocks[2];
@@ -638,6 +829,10 @@ hipError_t stage_cost(Runner& r, const Jobs& jobs) {
             const int64_t slices = (HW * j->N + kThreads * cpt - 1) / (kThreads * cpt);
             a.nblk = (uint32_t)std::max<int64_t>(1, (slices + stride - 1) / stride);
             const int t = j->dtype == LF_U8 ? 0 : 1, col = j->C == 3 ? 1 : 0;
+            if (j->full_range && !j->cost_f32) {
+                full[t][col].push_back(a);
+                continue;
+            }
             l2[t][col].push_back(a);
             l2_blocks[t][col].push_back(a.nblk);
         } else {
@@ -669,6 +864,10 @@ hipError_t stage_cost(Runner& r, const Jobs& jobs) {
         return e;
     if (!l2[1][1].empty() && (e = l2_walk<float, 3>(r, l2[1][1], l2_blocks[1][1])) != hipSuccess)
         return e;
+    if (!full[0][0].empty() && (e = l2_full<uint8_t, 1>(r, full[0][0])) != hipSuccess) return e;
+    if (!full[1][0].empty() && (e = l2_full<float, 1>(r, full[1][0])) != hipSuccess) return e;
+    if (!full[0][1].empty() && (e = l2_full<uint8_t, 3>(r, full[0][1])) != hipSuccess) return e;
+    if (!full[1][1].empty() && (e = l2_full<float, 3>(r, full[1][1])) != hipSuccess) return e;
     if (!ca[0].empty() &&
         (e = launch(r, kStCost, cost_census_kernel<Single<CensusAllArgs>, 1>,
                     cost_census_kernel<Group<CensusAllArgs>, 1>, ca[0], ca_blocks[0],

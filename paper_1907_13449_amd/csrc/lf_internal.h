@@ -232,6 +232,7 @@ struct Job {
     uint16_t* cost;           // [cells]
     float* cost_f32;          // [cells] or null
     int64_t cap_cells;
+    bool full_range;          // lo, hi are 0, N-1 everywhere, set here (no bounds given)
     void* sgm_ws;             // sgm_bounded_scratch_bytes
     void* csum;               // [cells] uint16 or uint32
     int16_t* d_index;         // [H*W]
