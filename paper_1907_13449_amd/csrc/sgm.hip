@@ -1813,14 +1813,18 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
     // with 16 paths (8,192) 382 / 254; 1080x1920, N = 96 (8,640) 1468 / 664.  Beyond
     // 128 hypotheses a lane of the one-line form holds three or four: N = 200, 256x256
     // (2,048) 94 / 95, 384x384 (3,072) 190 / 141, 375x450 with 16 paths 458 / 181.
-    uint64_t steps = 0, longest = 1;
-    int widest = 0;
+    // The light fields of a batch with up to 128 hypotheses count, and run, together: a
+    // launch takes its longest line's time at least (six light fields, N = 33 .. 96, of
+    // 89x197 to 317x414: 336 us by two launches of one line per wave, 411 us by two of
+    // four, 263 us by one of four).
+    uint64_t steps[2] = {0, 0}, longest[2] = {1, 1};  // up to 128 hypotheses, more
+    int widest = 0;                                // of the former
     for (const Job* j : jobs) {
-        steps += (uint64_t)j->H * j->W * j->prm.sgm_final.npaths;
-        longest = std::max(longest, (uint64_t)std::max(j->H, j->W));
-        widest = std::max(widest, j->N);
+        const int big = j->N > 128;
+        steps[big] += (uint64_t)j->H * j->W * j->prm.sgm_final.npaths;
+        longest[big] = std::max(longest[big], (uint64_t)std::max(j->H, j->W));
+        if (!big) widest = std::max(widest, j->N);
     }
-    const bool many = r.tune.bounded_lanes < 64 || steps > longest * (widest > 128 ? 2300 : 4500);
     for (const Job* j : jobs) {
         const int H = j->H, W = j->W, N = j->N;
         const size_t HW = (size_t)H * W;
@@ -1829,6 +1833,8 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
         uint16_t* Lbuf = (uint16_t*)((char*)j->sgm_ws + round256(HW * sizeof(PixMeta)));
         const size_t dir_stride = HW * N;          // worst-case cells per direction
 
+        const int big = N > 128;
+        const bool many = r.tune.bounded_lanes < 64 || steps[big] > longest[big] * (big ? 2300 : 4500);
         if (many && r.tune.bounded_offsets == 32 && dir_stride * 2 + 4 <= (size_t)INT32_MAX) {
             RowsArgs w{};
             w.cost = j->cost;
@@ -1844,7 +1850,7 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
             w.P2 = (uint32_t)sp.P2;
             w.npaths = sp.npaths;
             rows_waves(H, W, sp.npaths, w.wbase);
-            rows[N <= 64 ? 0 : N <= 128 ? 1 : 2].push_back(w);
+            rows[big ? 2 : widest <= 64 ? 0 : 1].push_back(w);
         } else {
             meta.push_back(MetaArgs{j->offsets, j->lo, j->hi, pm, (int)HW, N});
             meta_blocks.push_back(div_up(HW, 256));
