@@ -5,6 +5,8 @@
 // per pixel, coalesced along rows.
 #include "lf_internal.h"
 
+#include <type_traits>
+
 namespace lf {
 namespace {
 
@@ -388,8 +390,11 @@ struct WtaArgs {
 // its widest pixel (79 us of 37 M 32-bit costs, 1080 x 1920 pixels, an eighth of which
 // have 96 hypotheses; 90 us of 512^2 x 100).  So a lane loads a narrow pixel's costs 8 at
 // a time, and wide pixels are left to 16 lanes each, which load neighbouring costs.
-// Now 38 and 21 us; the bytes take 38 and 21 us at the rate of a large copy.
-constexpr int kNarrow = 16;        // hypotheses of the widest narrow pixel: two rounds
+// Now 38 and 22 us; the bytes take 38 and 21 us at the rate of a large copy.
+// Four rounds are still quicker than leaving the pixel to others where the image is too
+// small to hide their latency: 175 x 294, N = 30, 4.8 us, with 16 here 6.8 us (10.3 us if
+// the 16 lanes also took one pixel at a time).
+constexpr int kNarrow = 32;        // hypotheses of the widest narrow pixel
 
 // 8 consecutive costs.
 __device__ __forceinline__ void ld8(const uint32_t* c, uint32_t (&x)[8]) {
@@ -465,27 +470,52 @@ __device__ __forceinline__ void wta_pixels(const WtaArgs& a, int p, WideLds& wl)
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const int count = __popcll(wides), sub = lane & 15;
-        for (int r = 0; r < count; r += 4) {
-            const int i = min(r + (lane >> 4), count - 1);  // the last one again: the same
-            const int packed = wl.n[i], m = packed & 0xFFFF;
-            const SumT* __restrict__ w = csum + wl.off[i];
-            uint32_t least = 0;
-            int at = 0;
-            for (int k0 = sub; k0 < m; k0 += 128) {
-                uint32_t x[8];
+        // Q pixels at a time per 16 lanes, 8 loads in flight for them together
+        auto search = [&](int r, auto kQ) {
+            constexpr int Q = decltype(kQ)::value, L = 8 / Q;
+            const SumT* __restrict__ w[Q];
+            int m[Q], owner[Q], at[Q], longest = 0;
+            uint32_t least[Q];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) x[j] = w[min(k0 + 16 * j, m - 1)];
-                if (k0 == sub) least = x[0], at = sub;
+            for (int q = 0; q < Q; ++q) {
+                // past the last one: that again
+                const int i = min(r + 4 * q + (lane >> 4), count - 1);
+                w[q] = csum + wl.off[i];
+                m[q] = wl.n[i] & 0xFFFF;
+                owner[q] = wl.n[i] >> 16;
+                longest = max(longest, m[q]);
+                least[q] = ~0u;
+                at[q] = INT_MAX;                  // any real one is before it
+            }
+            for (int k0 = sub; k0 < longest; k0 += 16 * L) {
+                uint32_t x[Q][L];
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (k0 + 16 * j < m && x[j] < least) {
-                        least = x[j];
-                        at = k0 + 16 * j;
+                for (int q = 0; q < Q; ++q)
+#pragma unroll
+                    for (int j = 0; j < L; ++j) x[q][j] = w[q][min(k0 + 16 * j, m[q] - 1)];
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+#pragma unroll
+                    for (int j = 0; j < L; ++j) {
+                        const int k = k0 + 16 * j;
+                        if (k < m[q] && (x[q][j] < least[q] || at[q] == INT_MAX)) {
+                            least[q] = x[q][j];
+                            at[q] = k;
+                        }
                     }
             }
-            const uint32_t all = row_least(least);
-            const uint32_t first = row_least(least == all ? (uint32_t)at : ~0u);
-            if (sub == 0) wl.best[packed >> 16] = (int)first;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const uint32_t all = row_least(least[q]);
+                const uint32_t first = row_least(least[q] == all ? (uint32_t)at[q] : ~0u);
+                if (sub == 0) wl.best[owner[q]] = (int)first;
+            }
+        };
+        for (int r = 0; r < count;) {                       // uniform
+            const int left = count - r;
+            if (left > 8) search(r, std::integral_constant<int, 4>()), r += 16;
+            else if (left > 4) search(r, std::integral_constant<int, 2>()), r += 8;
+            else search(r, std::integral_constant<int, 1>()), r += 4;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         if (wide) {

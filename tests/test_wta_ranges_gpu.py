@@ -1,7 +1,7 @@
 """The winner search and the median against the oracle: winners and disparities of given
 aggregated costs, bit-exact (the same float32 operations).
 
-Range widths sit around the limits of the search: 8 hypotheses are one round of loads, 16
+Range widths sit around the limits of the search: 8 hypotheses are one round of loads, 32
 the widest pixel that a single lane searches, 128 the hypotheses of one round of 16
 lanes; costs are small numbers, so that ties are frequent, or the largest ones; maps
 are narrower than a workgroup, a window or a median's four rows, and the last pixels'
@@ -19,6 +19,7 @@ torch = pytest.importorskip("torch")
     (37, 61, 100, [7, 7, 7, 100], 32, 40),
     (37, 61, 100, [1, 2, 8, 9, 15, 16, 17, 100], 16, 40),
     (21, 67, 256, [127, 128, 129, 255, 256], 32, 3),
+    (21, 67, 40, [31, 32, 33], 16, 20),
     (21, 67, 256, [1, 256], 16, 3),
     (1, 300, 13, [1, 5, 13], 32, 2 ** 32 - 1),
     (301, 1, 17, [16, 17], 16, 2 ** 16 - 1),
