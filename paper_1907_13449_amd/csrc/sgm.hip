@@ -1,7 +1,8 @@
 // Semi-global matching, Eq. (8)-(10), on gfx950.
 //
 // Schedule.  All path directions of all views run in ONE launch: a wavefront
-// owns one path line of one direction of one view, and writes that direction's
+// owns one path line (or four, see the kernels with 16 lanes per line) of one
+// direction of one view, and writes that direction's
 // path costs L_r to a buffer of its own (no read-modify-write, no atomics); a
 // second kernel sums the directions, Eq. (9), and for the initial stage takes
 // the WTA of Eq. (10) in the same pass.  With 8 directions x |V| views the launch
@@ -447,7 +448,7 @@ __device__ __forceinline__ void stage_put(uint8_t* dst, const uint32_t (&L)[K]) 
     }
 }
 
-// kPad (8-bit path costs, K <= 2, and B + 2 P2 <= 255 + P1 for the largest Census
+// kPad (8-bit path costs, K = 2, and B + 2 P2 <= 255 + P1 for the largest Census
 // cost B): hypotheses k >= N read the 255 that pads each cost row instead of
 // adding kInf.  Their path costs then stay >= 255 while every real one stays
 // <= B + P2 <= 255, so they never lower the minimum m, and as the neighbour of
@@ -634,6 +635,279 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void sgm_dense_paths_kernel(Sr
             if (line[part] < 0) break;
             dense_line<K, LT, D, kPad>(a, z, locate(a.lines, a.H, a.W, line[part]), wst);
         }
+    }
+}
+
+// --- 16 lanes (one DPP row) per path line, four lines per wave ----------------
+// The lines of a direction are taken as units of equal length: the
+// primary axis is the one the direction moves fastest along (the shorter one for
+// the diagonals), and unit x walks it from its entry side, starting at position
+// x of the other axis and, where the direction also moves along that one,
+// wrapping around its end.  A path starts (L = C) at the first step and at each
+// wrap, which is where the predecessor is outside the image.  A knight move
+// steps two along its primary axis: one set of units per parity.  A wave's four
+// rows take four neighbouring units, so they walk side by side.
+
+// The walk of direction (du, dv) as equal units.
+struct Walk {
+    bool pv;            // the primary axis is v
+    int step, dir;      // pixels per step along it, and its sign
+    int len, Q;         // lengths of the primary and the other axis
+    int dsec;           // movement along the other axis per step: -1, 0, 1
+    int units;          // Q for each parity of the primary axis
+};
+
+__host__ __device__ inline Walk make_walk(int H, int W, int du, int dv) {
+    const int au = du < 0 ? -du : du, av = dv < 0 ? -dv : dv;
+    Walk w;
+    w.pv = av > au || (av == au && H <= W);
+    w.step = av > au ? av : au;
+    w.dir = (w.pv ? dv : du) > 0 ? 1 : -1;
+    w.len = w.pv ? H : W;
+    w.Q = w.pv ? W : H;
+    w.dsec = w.pv ? du : dv;
+    w.units = w.Q * (w.step < w.len ? w.step : w.len);
+    return w;
+}
+
+// The waves of the directions, four units each, and their prefix sums.
+inline void rows_waves(int H, int W, int npaths, int* wbase) {
+    int n = 0;
+    wbase[0] = 0;
+    for (int r = 0; r < kMaxPaths; ++r) {
+        if (r < npaths) n += (make_walk(H, W, kDirs[r][0], kDirs[r][1]).units + 3) / 4;
+        wbase[r + 1] = n;
+    }
+}
+
+// Lane j of every row takes lane I's value of its row.
+template <int I>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + I, 0xF, 0xF, true);
+}
+
+// The same in a register of its own, for values that are subtracted or shifted by:
+// the compiler folds a DPP operand into the reversed forms too (v_subrev,
+// v_lshrrev), which permute the other operand (measured).
+template <int I>
+__device__ __forceinline__ uint32_t row_value(uint32_t v) {
+    uint32_t x = row_bcast<I>(v);
+    asm("" : "+v"(x));
+    return x;
+}
+
+// Row rotations: the value of lane j - 1 and of lane j + 1 (mod 16).
+__device__ __forceinline__ uint32_t row_prev(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t row_next(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x12F, 0xF, 0xF, true);
+}
+
+// Minimum over each row of 16 lanes, in every lane of it (rotations by 8, 4, 2, 1).
+__device__ __forceinline__ uint32_t row_min(uint32_t v) {
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, true));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xF, 0xF, true));
+    return min(v, row_prev(v));
+}
+
+// The steps at which any of the four rows has its bit set.
+__device__ __forceinline__ uint32_t any_row(uint64_t ballot) {
+    const uint32_t half = (uint32_t)ballot | (uint32_t)(ballot >> 32);
+    return (half | half >> 16) & 0xFFFFu;
+}
+
+// Two 16-bit values per register.
+using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
+using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
+using u16x2 = unsigned short __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 as_u16x2(uint32_t x) { return __builtin_bit_cast(u16x2, x); }
+__device__ __forceinline__ uint32_t as_u32(u16x2 x) { return __builtin_bit_cast(uint32_t, x); }
+__device__ __forceinline__ uint32_t pk_min(uint32_t x, uint32_t y) {
+    return as_u32(__builtin_elementwise_min(as_u16x2(x), as_u16x2(y)));
+}
+__device__ __forceinline__ uint32_t pk_add(uint32_t x, uint32_t y) {
+    return as_u32(as_u16x2(x) + as_u16x2(y));
+}
+__device__ __forceinline__ uint32_t pk_sub(uint32_t x, uint32_t y) {
+    return as_u32(as_u16x2(x) - as_u16x2(y));
+}
+__device__ __forceinline__ uint32_t pk_add_sat(uint32_t x, uint32_t y) {
+    return as_u32(__builtin_elementwise_add_sat(as_u16x2(x), as_u16x2(y)));
+}
+// (x >> 16) | (y << 16): the high half of x and the low half of y.
+__device__ __forceinline__ uint32_t pk_next(uint32_t x, uint32_t y) {
+    return __builtin_amdgcn_alignbit(y, x, 16);
+}
+
+// The initial paths, four lines per wave: lane j of a row holds the 2 NR hypotheses from
+// 2 NR j, two per register in packed 16-bit arithmetic.  The one-line form is bound by the
+// issue of its instructions, 25 per step; this one takes 55 for a step of four lines.
+// A byte permutation unpacks the lane's cost bytes and puts 255 in place of hypotheses
+// k >= N (the bound of kPad: those then never win a min).  Lane j holds the pixel of step
+// j of a block of 16, as byte offsets, and a step reads them by a row broadcast; the
+// next block's costs are in flight.  A row's path costs are written by one instruction
+// (past the caches where the rows are whole lines: 286 us, 4 views of 512x512, N = 100,
+// for 389 through them; 344 us by the one-line form, 1.07 GB written).
+struct DenseRowsArgs {
+    gptr<const uint8_t> cvol;      // [nv][H*W][NPc]
+    gptr<uint8_t> Lbuf;            // [npaths][nv][H*W][NP]
+    int nv, H, W, N, NP, NPc;
+    uint32_t P1, P2;
+    int npaths;
+    uint32_t wblocks;              // blocks per view
+    int wbase[kMaxPaths + 1];      // direction r owns waves [wbase[r], wbase[r+1])
+};
+
+constexpr uint32_t kRowsVolume = 0x7F000000u;  // the largest volume of a view
+
+template <int NR>
+__device__ __forceinline__ void dense_rows_wave(const DenseRowsArgs& a, int z, int wave) {
+    constexpr int B = 16;                          // steps per block
+    constexpr int NW = NR / 2;                     // words of a lane's costs
+    const int lane = threadIdx.x & 63, j = lane & 15, row = lane >> 4;
+    const int H = a.H, W = a.W, N = a.N;
+
+    // the wave's direction (constant indices: the record stays in registers)
+    int r = 0, wb = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxPaths; ++i)
+        if (i < a.npaths && wave >= a.wbase[i]) {
+            r = i;
+            wb = a.wbase[i];
+        }
+    const Walk wk = make_walk(H, W, dir_u(r), dir_v(r));
+    const int x = (wave - wb) * 4 + row;                      // this row's unit
+    const int xq = min(x, wk.units - 1);
+    const int q = xq / wk.Q, sec0 = xq - q * wk.Q;            // parity, start
+    const int P = (wk.len - q + wk.step - 1) / wk.step;       // steps of this unit
+    const int steps = (wk.len + wk.step - 1) / wk.step;       // of the wave
+    const int Prow = x < wk.units ? P : 0;                    // none past the last unit
+
+    const uint32_t HW = (uint32_t)H * W;
+    const uint32_t NPc = (uint32_t)a.NPc, NP = (uint32_t)a.NP;
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((const uint8_t*)a.cvol + (size_t)z * HW * NPc), (short)0, (int)(HW * NPc),
+        0x00020000);
+    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((uint8_t*)a.Lbuf + ((size_t)r * a.nv + z) * HW * NP), (short)0, (int)(HW * NP),
+        0x00020000);
+    // past the volumes (of at most kRowsVolume bytes), also one added to the other
+    constexpr uint32_t kNowhere = 0x80000000u, kNoLane = kRowsVolume;
+    // the lane's bytes of a cost row (the row's last ones, if it has none), and of a
+    // path-cost row
+    const uint32_t first = (uint32_t)min(2 * NR * j, a.NPc - 2 * NR);
+    const uint32_t out = 2 * NR * j < a.NP ? (uint32_t)(2 * NR * j) : kNoLane;
+    uint32_t sel[NR];                              // of the byte permutation
+#pragma unroll
+    for (int c = 0; c < NR; ++c) {
+        const int k = 2 * NR * j + 2 * c;          // 13: 0xFF, 12: 0
+        sel[c] = (k < N ? (uint32_t)k - first : 13u) |
+                 (k + 1 < N ? (uint32_t)k + 1 - first : 13u) << 16 | 0x0C000C00u;
+    }
+
+    // the steps of a block, one per lane of a row
+    struct Meta {
+        uint32_t cost, L;                          // byte offsets of the rows
+        uint32_t start;                            // a path starts
+        uint32_t starts;                           // steps at which any row's does
+    };
+    int tau = j;                                   // this lane's step
+    int sec = sec0 + wk.dsec * (j % wk.Q);         // and where it is
+    if (sec >= wk.Q) sec -= wk.Q;
+    if (sec < 0) sec += wk.Q;
+    const int adv = wk.dsec * (B % wk.Q);
+    auto next_meta = [&]() -> Meta {
+        const int st = q + wk.step * min(tau, P - 1);
+        const int pri = wk.dir > 0 ? st : wk.len - 1 - st;
+        const uint32_t p = (uint32_t)(wk.pv ? pri * W + sec : sec * W + pri);
+        Meta m;
+        m.cost = p * NPc;
+        m.L = tau < Prow ? p * NP : kNowhere;
+        m.start = tau == 0 || (wk.dsec > 0 && sec == 0) || (wk.dsec < 0 && sec == wk.Q - 1);
+        m.starts = any_row(__builtin_amdgcn_ballot_w64(m.start != 0));
+        tau += B;
+        sec += adv;
+        if (sec >= wk.Q) sec -= wk.Q;
+        if (sec < 0) sec += wk.Q;
+        return m;
+    };
+    struct Words {
+        uint32_t w[NW];
+    };
+    auto load = [&](uint32_t at) {
+        Words x;
+        if constexpr (NW == 2) {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rc, at, 0, 0);
+            x.w[0] = v[0];
+            x.w[1] = v[1];
+        } else {
+            x.w[0] = __builtin_amdgcn_raw_buffer_load_b32(rc, at, 0, 0);
+        }
+        return x;
+    };
+
+    const uint32_t P11 = a.P1 | a.P1 << 16, P22 = a.P2 | a.P2 << 16;
+    uint32_t L[NR], mm = 0;                        // mm: the minimum, in both halves
+#pragma unroll
+    for (int c = 0; c < NR; ++c) L[c] = 0;
+    Meta cur = next_meta();
+    Words cb[B];
+    static_for<B>([&](auto I) { cb[I] = load(row_value<I>(cur.cost) + first); });
+    for (int base = 0; base < steps; base += B) {
+        const Meta nxt = next_meta();
+        static_for<B>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            uint32_t C[NR], X[NR], nb[NR + 1];
+#pragma unroll
+            for (int c = 0; c < NR; ++c)
+                C[c] = __builtin_amdgcn_perm(cb[i].w[NW - 1], cb[i].w[0], sel[c]);
+            cb[i] = load(row_value<i>(nxt.cost) + first);
+#pragma unroll
+            for (int c = 0; c < NR; ++c) X[c] = pk_add(L[c], P11);
+            nb[0] = pk_next(dpp<0x111>(~0u, X[NR - 1]), X[0]);          // row_shr:1
+#pragma unroll
+            for (int c = 1; c < NR; ++c) nb[c] = pk_next(X[c - 1], X[c]);
+            nb[NR] = pk_next(X[NR - 1], dpp<0x101>(~0u, X[0]));         // row_shl:1
+            const uint32_t m2 = pk_add(mm, P22);
+#pragma unroll
+            for (int c = 0; c < NR; ++c)
+                L[c] = pk_add(pk_min(pk_min(L[c], m2), pk_min(nb[c], nb[c + 1])),
+                              pk_sub(C[c], mm));
+            if (__builtin_expect(cur.starts >> i & 1, 0)) {
+                const bool start = row_value<i>(cur.start) != 0;
+#pragma unroll
+                for (int c = 0; c < NR; ++c) L[c] = start ? C[c] : L[c];
+            }
+            uint32_t least = L[0];
+#pragma unroll
+            for (int c = 1; c < NR; ++c) least = pk_min(least, L[c]);
+            least = pk_min(least, __builtin_amdgcn_alignbit(least, least, 16));
+            mm = row_min(least);                   // both halves alike: ordered as one
+            const uint32_t at = row_value<i>(cur.L) + out;
+            if constexpr (NW == 2)                 // whole lines, read once by the sum
+                __builtin_amdgcn_raw_buffer_store_b64(
+                    u32x2{__builtin_amdgcn_perm(L[1], L[0], 0x06040200u),
+                          __builtin_amdgcn_perm(L[3], L[2], 0x06040200u)}, ro, at, 0, 2);
+            else
+                __builtin_amdgcn_raw_buffer_store_b32(
+                    __builtin_amdgcn_perm(L[1], L[0], 0x06040200u), ro, at, 0, 0);
+        });
+        cur = nxt;
+    }
+}
+
+template <class Src, int NR>
+__global__ __launch_bounds__(64 * kWavesPerBlock) void sgm_dense_rows_kernel(Src src) {
+    for (uint32_t vb = blockIdx.x; vb < src.total; vb += gridDim.x) {
+        uint32_t b;
+        const DenseRowsArgs& a = member(src, vb, b);
+        const int z = (int)(b / a.wblocks);                   // the view
+        const uint32_t wb = b - (uint32_t)z * a.wblocks;
+        const int wave = __builtin_amdgcn_readfirstlane(wb * kWavesPerBlock + (threadIdx.x >> 6));
+        if (wave >= a.wbase[kMaxPaths]) continue;             // wave-uniform
+        dense_rows_wave<NR>(a, z, wave);
     }
 }
 
@@ -1036,15 +1310,6 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void sgm_bounded_paths_kernel(
 // that has 0xFFFF on both sides (a narrow window takes one hypothesis more to each
 // side, hence at most 14).
 //
-// Lines.  The lines of a direction are taken as units of equal length: the
-// primary axis is the one the direction moves fastest along (the shorter one for
-// the diagonals), and unit x walks it from its entry side, starting at position
-// x of the other axis and, where the direction also moves along that one,
-// wrapping around its end.  A path starts (L = C) at the first step and at each
-// wrap, which is where the predecessor is outside the image.  A knight move
-// steps two along its primary axis: one set of units per parity.  A wave's four
-// rows take four neighbouring units, so they walk side by side.
-//
 // Metadata.  Lane j of a row holds what step j of the current block of 16 steps
 // needs (bounds, cell offset), decoded once, and a step reads it by a row
 // broadcast (row_newbcast) fused into the instruction that uses it; the next
@@ -1064,70 +1329,6 @@ struct RowsArgs {
     int wbase[kMaxPaths + 1];      // direction r owns waves [wbase[r], wbase[r+1])
 };
 
-// The walk of direction (du, dv) as equal units.
-struct Walk {
-    bool pv;            // the primary axis is v
-    int step, dir;      // pixels per step along it, and its sign
-    int len, Q;         // lengths of the primary and the other axis
-    int dsec;           // movement along the other axis per step: -1, 0, 1
-    int units;          // Q for each parity of the primary axis
-};
-
-__host__ __device__ inline Walk make_walk(int H, int W, int du, int dv) {
-    const int au = du < 0 ? -du : du, av = dv < 0 ? -dv : dv;
-    Walk w;
-    w.pv = av > au || (av == au && H <= W);
-    w.step = av > au ? av : au;
-    w.dir = (w.pv ? dv : du) > 0 ? 1 : -1;
-    w.len = w.pv ? H : W;
-    w.Q = w.pv ? W : H;
-    w.dsec = w.pv ? du : dv;
-    w.units = w.Q * (w.step < w.len ? w.step : w.len);
-    return w;
-}
-
-// The waves of the directions, four units each, and their prefix sums.
-inline void rows_waves(int H, int W, int npaths, int* wbase) {
-    int n = 0;
-    wbase[0] = 0;
-    for (int r = 0; r < kMaxPaths; ++r) {
-        if (r < npaths) n += (make_walk(H, W, kDirs[r][0], kDirs[r][1]).units + 3) / 4;
-        wbase[r + 1] = n;
-    }
-}
-
-// Lane j of every row takes lane I's value of its row.
-template <int I>
-__device__ __forceinline__ uint32_t row_bcast(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + I, 0xF, 0xF, true);
-}
-
-// The same in a register of its own, for values that are subtracted or shifted by:
-// the compiler folds a DPP operand into the reversed forms too (v_subrev,
-// v_lshrrev), which permute the other operand (measured).
-template <int I>
-__device__ __forceinline__ uint32_t row_value(uint32_t v) {
-    uint32_t x = row_bcast<I>(v);
-    asm("" : "+v"(x));
-    return x;
-}
-
-// Row rotations: the value of lane j - 1 and of lane j + 1 (mod 16).
-__device__ __forceinline__ uint32_t row_prev(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xF, 0xF, true);
-}
-__device__ __forceinline__ uint32_t row_next(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x12F, 0xF, 0xF, true);
-}
-
-// Minimum over each row of 16 lanes, in every lane of it (rotations by 8, 4, 2, 1).
-__device__ __forceinline__ uint32_t row_min(uint32_t v) {
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true));
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, true));
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xF, 0xF, true));
-    return min(v, row_prev(v));
-}
-
 // What the four rows need of the 16 steps of a block: lane j of a row holds step
 // j of its line.
 struct RowsMeta {
@@ -1145,36 +1346,7 @@ constexpr uint32_t kRowWide = 1,    // a wide pixel
     kRowConv = 8,                   // wide, but not after a wide one from the same lo
     kRowAfterWide = 16;             // the pixel before is a wide one
 
-// The steps at which any of the four rows has its bit set.
-__device__ __forceinline__ uint32_t any_row(uint64_t ballot) {
-    const uint32_t half = (uint32_t)ballot | (uint32_t)(ballot >> 32);
-    return (half | half >> 16) & 0xFFFFu;
-}
-
 constexpr int kRowsNarrow = 14;        // the widest window of the narrow path
-
-// Two 16-bit values per register.
-using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
-using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
-using u16x2 = unsigned short __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u16x2 as_u16x2(uint32_t x) { return __builtin_bit_cast(u16x2, x); }
-__device__ __forceinline__ uint32_t as_u32(u16x2 x) { return __builtin_bit_cast(uint32_t, x); }
-__device__ __forceinline__ uint32_t pk_min(uint32_t x, uint32_t y) {
-    return as_u32(__builtin_elementwise_min(as_u16x2(x), as_u16x2(y)));
-}
-__device__ __forceinline__ uint32_t pk_add(uint32_t x, uint32_t y) {
-    return as_u32(as_u16x2(x) + as_u16x2(y));
-}
-__device__ __forceinline__ uint32_t pk_sub(uint32_t x, uint32_t y) {
-    return as_u32(as_u16x2(x) - as_u16x2(y));
-}
-__device__ __forceinline__ uint32_t pk_add_sat(uint32_t x, uint32_t y) {
-    return as_u32(__builtin_elementwise_add_sat(as_u16x2(x), as_u16x2(y)));
-}
-// (x >> 16) | (y << 16): the high half of x and the low half of y.
-__device__ __forceinline__ uint32_t pk_next(uint32_t x, uint32_t y) {
-    return __builtin_amdgcn_alignbit(y, x, 16);
-}
 
 // LDS of one row's wide path costs: 16 lanes x 2 NR hypotheses, with as many
 // entries of 0xFFFF before and after them.
@@ -1589,11 +1761,10 @@ hipError_t dense_variant(Runner& r, const std::vector<DenseArgs>& args,
 }
 
 // v: 0 8-bit path costs, 1 16-bit, 2 8-bit with the padded rows standing in for
-// kInf (K <= 2 only)
+// kInf (K = 2 only: up to 64 hypotheses take four lines per wave)
 hipError_t dense_k(Runner& r, int K, int v, const std::vector<DenseArgs>& args,
                    const std::vector<uint32_t>& blocks) {
-    if (v == 2) return K == 1 ? dense_variant<1, uint8_t, true>(r, args, blocks)
-                              : dense_variant<2, uint8_t, true>(r, args, blocks);
+    if (v == 2) return dense_variant<2, uint8_t, true>(r, args, blocks);
     if (v == 1) {
         switch (K) {
             case 1: return dense_variant<1, uint16_t, false>(r, args, blocks);
@@ -1645,6 +1816,15 @@ hipError_t bounded_rows(Runner& r, const std::vector<RowsArgs>& args) {
                   64 * kWavesPerBlock);
 }
 
+template <int NR>
+hipError_t dense_rows(Runner& r, const std::vector<DenseRowsArgs>& args) {
+    std::vector<uint32_t> blocks;
+    for (const DenseRowsArgs& a : args) blocks.push_back(a.wblocks * a.nv);
+    return launch(r, kStInitPaths, sgm_dense_rows_kernel<Single<DenseRowsArgs>, NR>,
+                  sgm_dense_rows_kernel<Group<DenseRowsArgs>, NR>, args, blocks,
+                  64 * kWavesPerBlock);
+}
+
 hipError_t bounded_k(Runner& r, int K, const std::vector<BoundedArgs>& args,
                      const std::vector<uint32_t>& blocks) {
     switch (K) {
@@ -1690,12 +1870,38 @@ hipError_t stage_sgm_initial(Runner& r, const Jobs& jobs, int part) {
     // variants: K in 1..4 x (8-bit, 16-bit, 8-bit with padded rows)
     std::vector<DenseArgs> dense[4][3];
     std::vector<uint32_t> dense_blocks[4][3];
+    std::vector<DenseRowsArgs> drows[2];           // up to 64, 128 hypotheses
     std::vector<SumWtaArgs> sums[2][2];            // [8/16-bit path costs][8/16 paths]
     std::vector<uint32_t> sum_blocks[2][2];
     std::vector<SumWtaArgs> rows[2];               // 8-bit rows <= 128 B: [8/16 paths]
     std::vector<uint32_t> row_blocks[2];
     std::vector<ExportArgs> ex_cost, ex_sum;       // outputs for checking
     std::vector<uint32_t> ex_cost_blocks, ex_sum_blocks;
+    // Four lines per wave, or one (8-bit path costs with the bound of kPad; paths in us, one
+    // line against four).  Up to 64 hypotheses four are the faster at every size tried:
+    // 4 views of 512x512, N = 40, 272 / 157, of 96x96, N = 32, 24 / 17; 2 of 24x1900,
+    // N = 60, 196 / 191, of 1080x1920, N = 64, 1259 / 975.  With more, a step of a line
+    // takes longer than in the one-line form, so there have to be lines enough beside the
+    // longest one, counted as all path steps over that one's: 53x1674, N = 100 (1,696)
+    // 264 / 333; 32x400, 16 paths, N = 128 (2,048) 76 / 77; 128x128, N = 100 (4,096)
+    // 35 / 24; 512x512, N = 100, 371 / 295.  And as the lines of all directions are then
+    // walked at once, the Census costs have to stay in the 256 MB cache beside the path
+    // costs: 256x1024, N = 65 (71 MB) 338 / 291; 2 views of 720x1280, N = 96 (181 MB) 554 /
+    // 599, of 1080x1920 (415 MB) 1370 / 1509; 4 of 1080x1080, N = 80 (392 MB) 1545 / 1579.
+    auto fits_rows = [](const Job* j) {
+        const int bits = j->C * census_bits(j->prm.census);
+        const int64_t cells = (int64_t)j->H * j->W * std::max(dense_cvol_np(j->N), dense_lnp(j->N, 1));
+        return j->N <= 128 && bits + j->prm.sgm_init.P2 <= 255 &&
+               bits + 2 * j->prm.sgm_init.P2 <= 255 + j->prm.sgm_init.P1 &&
+               cells <= (int64_t)kRowsVolume &&
+               (j->N <= 64 || (int64_t)j->nv * j->H * j->W * dense_cvol_np(j->N) <= (int64_t)128 << 20);
+    };
+    uint64_t steps = 0, longest = 1;               // of those with more than 64 hypotheses
+    for (const Job* j : jobs)
+        if (j->N > 64 && fits_rows(j)) {
+            steps += (uint64_t)j->nv * j->H * j->W * j->prm.sgm_init.npaths;
+            longest = std::max(longest, (uint64_t)std::max(j->H, j->W));
+        }
     for (const Job* j : jobs) {
         const int H = j->H, W = j->W, N = j->N, NPc = dense_cvol_np(N);
         const size_t HW = (size_t)H * W;
@@ -1742,8 +1948,26 @@ hipError_t stage_sgm_initial(Runner& r, const Jobs& jobs, int part) {
         d.wblocks = div_up(d.units.nunits, kWavesPerBlock);
         const int K = (N + 63) / 64 - 1;
         const int v = lt == 0 && K <= 1 && bits + 2 * sp.P2 <= 255 + sp.P1 ? 2 : lt;
-        dense[K][v].push_back(d);
-        dense_blocks[K][v].push_back(d.wblocks * j->nv);
+        if (fits_rows(j) && (N <= 64 || steps > 2048 * longest)) {
+            DenseRowsArgs w{};
+            w.cvol = cvol;
+            w.Lbuf = (uint8_t*)Lbuf;
+            w.nv = j->nv;
+            w.H = H;
+            w.W = W;
+            w.N = N;
+            w.NP = NP;
+            w.NPc = NPc;
+            w.P1 = d.P1;
+            w.P2 = d.P2;
+            w.npaths = sp.npaths;
+            rows_waves(H, W, sp.npaths, w.wbase);
+            w.wblocks = div_up(w.wbase[kMaxPaths], kWavesPerBlock);
+            drows[K].push_back(w);
+        } else {
+            dense[K][v].push_back(d);
+            dense_blocks[K][v].push_back(d.wblocks * j->nv);
+        }
 
         SumWtaArgs s{};
         s.Lbuf = Lbuf;
@@ -1798,6 +2022,8 @@ hipError_t stage_sgm_initial(Runner& r, const Jobs& jobs, int part) {
                 if ((e = dense_k(r, K + 1, v, dense[K][v], dense_blocks[K][v])) != hipSuccess)
                     return e;
             }
+        if (!drows[0].empty() && (e = dense_rows<2>(r, drows[0])) != hipSuccess) return e;
+        if (!drows[1].empty() && (e = dense_rows<4>(r, drows[1])) != hipSuccess) return e;
         return hipSuccess;
     }
     // the row-wise sums: one workgroup per 16 pixels (measured faster than
