@@ -317,7 +317,8 @@ typedef struct {
  * -- cells per thread of one slice of the bounded cost kernel; cost_stride: 1 (default), 2 or 4 --
  * slices each cost workgroup walks (persistent workgroups); dense_prefetch: 4, 8
  * or 16 (default) -- path steps of cost loads in flight per wave in the initial
- * SGM with one path line per wave (many hypotheses), also the steps whose path costs it stages before copying them out;
+ * SGM with one path line per wave (16-bit path costs, above 128 hypotheses, thin or
+ * large images), also the steps whose path costs it stages before copying them out;
  * bounded_prefetch: 4 (default), 8 or 16 -- pixel metadata steps in flight
  * per wave in the bounded SGM with 64 lanes per line (their costs run half as
  * many steps ahead); bounded_lanes: 16, 32 or 64 (default) -- lanes per path line
