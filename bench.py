@@ -70,26 +70,27 @@ PAPER_RUNTIME = {"seconds_per_map_median": 10 ** 0.25, "seconds_per_map_average"
 # they were taken on) and which profiled stage launches it.
 KERNEL_SOURCE = {
     "census_kernel": "census.hip", "census_cost_volume_kernel": "sgm.hip",
-    "sgm_dense_paths_kernel": "sgm.hip", "dense_sum_wta_rows_kernel": "sgm.hip",
+    "sgm_dense_rows_kernel": "sgm.hip", "sgm_dense_paths_kernel": "sgm.hip",
+    "dense_sum_wta_rows_kernel": "sgm.hip",
     "dense_sum_wta_kernel": "sgm.hip", "initial_export_kernel": "sgm.hip",
     "prep_kernel": "post.hip", "fuse_kernel": "post.hip", "fill_kernel": "post.hip",
     "borders_kernel": "post.hip", "full_range_kernel": "post.hip",
     "scan_reduce_kernel": "post.hip", "scan_apply_kernel": "post.hip",
     "pad_views_kernel": "cost.hip", "cost_l2_kernel": "cost.hip",
-    "cost_census_all_kernel": "cost.hip", "pix_meta_kernel": "sgm.hip",
-    "sgm_bounded_paths_kernel": "sgm.hip", "sgm_bounded_group_kernel": "sgm.hip",
+    "cost_l2_full_kernel": "cost.hip", "cost_census_kernel": "cost.hip", "pix_meta_kernel": "sgm.hip",
+    "sgm_bounded_paths_kernel": "sgm.hip", "sgm_bounded_rows_kernel": "sgm.hip",
     "bounded_sum_kernel": "sgm.hip", "wta_subpixel_kernel": "post.hip",
     "median3_kernel": "post.hip",
 }
 STAGE_KERNELS = {
     "census": ["census_kernel"],
-    "sgm_initial": ["census_cost_volume_kernel", "sgm_dense_paths_kernel",
-                    "dense_sum_wta_rows_kernel", "dense_sum_wta_kernel"],
+    "sgm_initial": ["census_cost_volume_kernel", "sgm_dense_rows_kernel",
+                    "sgm_dense_paths_kernel", "dense_sum_wta_rows_kernel", "dense_sum_wta_kernel"],
     "fuse_fill_borders": ["prep_kernel", "fuse_kernel", "fill_kernel", "borders_kernel"],
     "offsets": ["scan_reduce_kernel", "scan_apply_kernel"],
     "cost_inputs": ["pad_views_kernel"],
-    "cost_bounded": ["cost_l2_kernel", "cost_census_all_kernel"],
-    "sgm_bounded": ["pix_meta_kernel", "sgm_bounded_paths_kernel", "sgm_bounded_group_kernel",
+    "cost_bounded": ["cost_l2_kernel", "cost_l2_full_kernel", "cost_census_kernel"],
+    "sgm_bounded": ["pix_meta_kernel", "sgm_bounded_paths_kernel", "sgm_bounded_rows_kernel",
                     "bounded_sum_kernel"],
     "wta_subpixel_median": ["wta_subpixel_kernel", "median3_kernel"],
 }
@@ -1069,10 +1070,10 @@ def main():
                                       "bytes_per_cell": 1.0,
                                       "achieved_gbs": cells_initial / (stage_ms["initial_cost"]
                                                                        * 1e-3) / 1e9},
-        "sgm_dense_paths_kernel": {"ms": stage_ms["initial_paths"],
-                                   "bytes_per_cell": 1.0 + npaths,
-                                   "achieved_gbs": (1.0 + npaths) * cells_initial /
-                                   (stage_ms["initial_paths"] * 1e-3) / 1e9},
+        "sgm_dense_rows_kernel": {"ms": stage_ms["initial_paths"],
+                                  "bytes_per_cell": 1.0 + npaths,
+                                  "achieved_gbs": (1.0 + npaths) * cells_initial /
+                                  (stage_ms["initial_paths"] * 1e-3) / 1e9},
         "dense_sum_wta_rows_kernel": {"ms": stage_ms["initial_sum_wta"],
                                       "bytes_per_cell": float(npaths),
                                       "achieved_gbs": npaths * cells_initial /
@@ -1086,7 +1087,7 @@ def main():
     roofline = {"bound": "hbm", "achieved": ini["achieved_gbs"], "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": ini["frac_hbm"], "traffic": ini["traffic"],
                 "traffic_ratio": ini["traffic_ratio"], "stage": "sgm_initial",
-                "kernels": ["census_cost_volume_kernel", "sgm_dense_paths_kernel",
+                "kernels": ["census_cost_volume_kernel", "sgm_dense_rows_kernel",
                             "dense_sum_wta_rows_kernel"],
                 "launches": ini["launches"], "ms": ini["ms"],
                 "bytes_per_cell": 12.0 + 18.0 / N, "cells": cells_initial,
