@@ -201,7 +201,8 @@ size_t lf_cost_workspace_size(int32_t S, int32_t T, int32_t C, int32_t H, int32_
                               int32_t N, const lf_params* prm);
 
 /* Bounded matching cost over all views, Sec. 3.5:
- *  offsets <- exclusive prefix sum of the widths d_hi - d_lo + 1 ([H*W+1] int64);
+ *  offsets <- exclusive prefix sum of the widths d_hi - d_lo + 1 ([H*W+1] int64); a
+ *  pixel with d_hi = d_lo - 1 owns no cells;
  *  for every cell (p, k), k in [d_lo[p], d_hi[p]]:
  *   LF_COST_L2, Eq. (12): S = sum_t sum_s |L_ref(p) - B_{s,t}(p + shift)| in
  *     float32, t outer, s inner, from +0; shift sh = (float)(s_hat-s)*d_k and

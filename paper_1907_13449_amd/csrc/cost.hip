@@ -37,6 +37,16 @@ __device__ __forceinline__ int first_pixel(const int64_t* __restrict__ off, int 
     return p0;
 }
 
+// The same by one thread, among the pixels from p on.
+__device__ __forceinline__ int pixel_of(const int64_t* __restrict__ off, int p, int end,
+                                        int64_t c) {
+    while (end - p > 1) {
+        const int mid = p + (end - p) / 2;
+        if (off[mid] <= c) p = mid; else end = mid;
+    }
+    return p;
+}
+
 // ---------------------------------------------------------------------------
 // l2 cost, Eq. (12).  Work is dealt in equal slices of cells: slice i is the
 // cells [i*chunk, (i+1)*chunk) of the CSR volume, whatever pixels they belong
@@ -648,7 +658,7 @@ struct CensusAllArgs {
 constexpr int kCensusChunk = 2 * kThreads;
 
 struct CensusLds {
-    int rel[kCensusChunk];         // a pixel's first cell, from the slice's first
+    int rel[kCensusChunk + 1];     // a pixel's first cell, from the slice's first
     int16_t lo[kCensusChunk];
     int np;
 };
@@ -664,9 +674,9 @@ __device__ __forceinline__ void census_slice(const CensusAllArgs& a, uint32_t b,
     const int p0 = first_pixel(off, HW, c0);
     const int npx = min(kCensusChunk, HW - p0);
     const int v0 = p0 / W, u0 = p0 - v0 * W;
-    for (int i = threadIdx.x; i < npx; i += kThreads) {
+    for (int i = threadIdx.x; i <= npx; i += kThreads) {
         sl.rel[i] = (int)(off[p0 + i] - c0);
-        sl.lo[i] = a.lo[p0 + i];
+        if (i < npx) sl.lo[i] = a.lo[p0 + i];
     }
     if (threadIdx.x == 0) sl.np = 0;
     __syncthreads();
@@ -674,19 +684,26 @@ __device__ __forceinline__ void census_slice(const CensusAllArgs& a, uint32_t b,
     for (int i = threadIdx.x; i < npx; i += kThreads)
         if (sl.rel[i] < len && (i + 1 == npx || sl.rel[i + 1] >= len)) atomicMax(&sl.np, i + 1);
     __syncthreads();
-    const int np = sl.np;
+    const int np = sl.np, stop = min(sl.rel[npx], len);     // of the staged pixels' cells
     const int sh = (S - 1) / 2, th = (T - 1) / 2;
     const uint64_t* __restrict__ census = a.census;
     const uint64_t* __restrict__ cref = census + ((size_t)th * S + sh) * C * HW;
     for (int c = threadIdx.x; c < len; c += kThreads) {
-        int i = 0, end = np;                                // largest i with rel[i] <= c
-        while (end - i > 1) {
-            const int mid = (i + end) >> 1;
-            if (sl.rel[mid] <= c) i = mid; else end = mid;
+        int i = 0, k, u = u0, v = v0;
+        if (__builtin_expect(c < stop, 1)) {
+            int end = np;                                   // largest i with rel[i] <= c
+            while (end - i > 1) {
+                const int mid = (i + end) >> 1;
+                if (sl.rel[mid] <= c) i = mid; else end = mid;
+            }
+            k = sl.lo[i] + c - sl.rel[i];
+        } else {                                            // past the staged pixels, of
+            const int p = pixel_of(off, p0 + npx, HW, c0 + c);    // which some own no cell
+            i = p - p0;
+            k = a.lo[p] + (int)(c0 + c - off[p]);
         }
-        const int k = sl.lo[i] + c - sl.rel[i];
         if ((unsigned)k >= (unsigned)N) continue;
-        int v = v0, u = u0 + i;
+        u += i;
         if (u >= W) {
             v += u / W;
             u %= W;
