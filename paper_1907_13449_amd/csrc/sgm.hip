@@ -1500,6 +1500,14 @@ __device__ __forceinline__ void bounded_rows_wave(const RowsArgs& a, int wave, u
     };
 
     uint16_t* const lrow = lds + row * kRowsLds<NR>;          // this row's entries
+    // Between accesses of lrow by different lanes: the hardware keeps a wave's LDS accesses
+    // in their order, the compiler those on the two sides of this (entries are written as
+    // words and as halves, which it may take for different objects).
+    auto lds_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
     uint32_t MF[NR];                                          // full range: 0xFFFF past N
 #pragma unroll
     for (int c = 0; c < NR; ++c) {
@@ -1575,13 +1583,13 @@ __device__ __forceinline__ void bounded_rows_wave(const RowsArgs& a, int wave, u
                     uint32_t* const own = (uint32_t*)(lrow + PAD + 2 * NR * j);
 #pragma unroll
                     for (int c = 0; c < NR; ++c) own[c] = pw ? Wp[c] : ~0u;
+                    lds_order();
                     if (!pw && V < 0x10000u) lrow[PAD + ((J - pl) & 15u)] = (uint16_t)V;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    lds_order();
                     const int d = clampi((int)lo - (int)pl, 1 - PAD, PAD - 1);
                     __builtin_memcpy(Wp, lrow + PAD + d + 2 * NR * j, 4 * NR);
                     below = (uint32_t)lrow[PAD + d - 1] << 16;
+                    lds_order();
                 }
                 const uint32_t P11 = P1 | P1 << 16, mP2 = m + P2;
                 const uint32_t m2 = mP2 | mP2 << 16, mm2 = m | m << 16;
@@ -1662,12 +1670,11 @@ __device__ __forceinline__ void bounded_rows_wave(const RowsArgs& a, int wave, u
                     uint32_t* const own = (uint32_t*)(lrow + PAD + 2 * NR * j);
 #pragma unroll
                     for (int c = 0; c < NR; ++c) own[c] = Wp[c];
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    lds_order();
                     // hypotheses lo' - 1 .. lo' + 14 of the next window
                     const int d = (int)(nl - 1 + ((J + 1 - nl) & 15u) - lo);
                     Vn = lrow[PAD + clampi(d, -PAD, 2 * PAD - 1)];
+                    lds_order();
                 }
             }
           }
