@@ -653,9 +653,14 @@ struct CensusAllArgs {
     int64_t cap_cells;
     int S, T, H, W, N;
     uint32_t cap;
+    uint32_t nblk;                 // workgroups of this light field
 };
 
 constexpr int kCensusChunk = 2 * kThreads;
+// Workgroups of a launch at most.  A launch has fewer than 2^32 work items, 2^24 of these
+// workgroups, which volumes of 2^33 cells (worst case) would exceed; those walk their
+// slices instead.
+constexpr int64_t kCensusBlocks = 1 << 23;
 
 struct CensusLds {
     int rel[kCensusChunk + 1];     // a pixel's first cell, from the slice's first
@@ -664,11 +669,11 @@ struct CensusLds {
 };
 
 template <int C>
-__device__ __forceinline__ void census_slice(const CensusAllArgs& a, uint32_t b, CensusLds& sl) {
+__device__ __forceinline__ void census_slice(const CensusAllArgs& a, int64_t b, CensusLds& sl) {
     const int S = a.S, T = a.T, H = a.H, W = a.W, N = a.N;
     const int HW = H * W;
     const int64_t* __restrict__ off = a.off;
-    const int64_t total = min(off[HW], a.cap_cells), c0 = (int64_t)b * kCensusChunk;
+    const int64_t total = min(off[HW], a.cap_cells), c0 = b * kCensusChunk;
     if (c0 >= total) return;                                // uniform
     const int len = (int)min((int64_t)kCensusChunk, total - c0);
     const int p0 = first_pixel(off, HW, c0);
@@ -729,12 +734,41 @@ __device__ __forceinline__ void census_slice(const CensusAllArgs& a, uint32_t b,
     }
 }
 
-template <class Src, int C>
+template <class Src, bool Walk, int C>
 __global__ __launch_bounds__(kThreads) void cost_census_kernel(Src src) {
     __shared__ CensusLds sl;
     uint32_t b;
     const CensusAllArgs& a = member(src, blockIdx.x, b);
-    census_slice<C>(a, b, sl);
+    if constexpr (Walk) {
+        const int64_t total = min(a.off[a.H * a.W], a.cap_cells);
+        for (int64_t slice = b; slice * kCensusChunk < total; slice += a.nblk) {   // uniform
+            census_slice<C>(a, slice, sl);
+            __syncthreads();                      // LDS of the slice is read
+        }
+    } else {
+        census_slice<C>(a, b, sl);
+    }
+}
+
+template <int C>
+hipError_t census_walk(Runner& r, std::vector<CensusAllArgs>& args) {
+    auto slices = [](const CensusAllArgs& a) {    // in the worst case
+        return ((int64_t)a.H * a.W * a.N + kCensusChunk - 1) / kCensusChunk;
+    };
+    int64_t all = 0;
+    for (const CensusAllArgs& a : args) all += slices(a);
+    const bool walk = all > kCensusBlocks;
+    const int64_t most = std::max<int64_t>(1, kCensusBlocks / (int64_t)args.size());
+    std::vector<uint32_t> blocks;
+    for (CensusAllArgs& a : args) {
+        a.nblk = (uint32_t)(walk ? std::min(slices(a), most) : slices(a));
+        blocks.push_back(a.nblk);
+    }
+    return walk ? launch(r, kStCost, cost_census_kernel<Single<CensusAllArgs>, true, C>,
+                         cost_census_kernel<Group<CensusAllArgs>, true, C>, args, blocks, kThreads)
+                : launch(r, kStCost, cost_census_kernel<Single<CensusAllArgs>, false, C>,
+                         cost_census_kernel<Group<CensusAllArgs>, false, C>, args, blocks,
+                         kThreads);
 }
 
 template <typename T, bool Walk, int C>
@@ -821,7 +855,6 @@ hipError_t stage_cost(Runner& r, const Jobs& jobs) {
     std::vector<L2Args> full[2][2];
     std::vector<uint32_t> l2_blocks[2][2];
     std::vector<CensusAllArgs> ca[2];              // [gray/colour]
-    std::vector<uint32_t> ca_blocks[2];
     const int cpt = r.tune.cost_cpt == 2 || r.tune.cost_cpt == 8 ? r.tune.cost_cpt : 4;
     const int stride = std::max(1, r.tune.cost_stride);
     for (const Job* j : jobs) {
@@ -867,9 +900,7 @@ hipError_t stage_cost(Runner& r, const Jobs& jobs) {
             a.W = j->W;
             a.N = j->N;
             a.cap = (uint32_t)j->cap;
-            const int col = j->C == 3 ? 1 : 0;
-            ca[col].push_back(a);
-            ca_blocks[col].push_back((uint32_t)((HW * j->N + kCensusChunk - 1) / kCensusChunk));
+            ca[j->C == 3 ? 1 : 0].push_back(a);
         }
     }
     hipError_t e = hipSuccess;
@@ -885,14 +916,8 @@ hipError_t stage_cost(Runner& r, const Jobs& jobs) {
     if (!full[1][0].empty() && (e = l2_full<float, 1>(r, full[1][0])) != hipSuccess) return e;
     if (!full[0][1].empty() && (e = l2_full<uint8_t, 3>(r, full[0][1])) != hipSuccess) return e;
     if (!full[1][1].empty() && (e = l2_full<float, 3>(r, full[1][1])) != hipSuccess) return e;
-    if (!ca[0].empty() &&
-        (e = launch(r, kStCost, cost_census_kernel<Single<CensusAllArgs>, 1>,
-                    cost_census_kernel<Group<CensusAllArgs>, 1>, ca[0], ca_blocks[0],
-                    kThreads)) != hipSuccess)
-        return e;
-    if (!ca[1].empty())
-        e = launch(r, kStCost, cost_census_kernel<Single<CensusAllArgs>, 3>,
-                   cost_census_kernel<Group<CensusAllArgs>, 3>, ca[1], ca_blocks[1], kThreads);
+    if (!ca[0].empty() && (e = census_walk<1>(r, ca[0])) != hipSuccess) return e;
+    if (!ca[1].empty()) e = census_walk<3>(r, ca[1]);
     return e;
 }
 
