@@ -19,6 +19,10 @@ namespace lf {
 namespace {
 
 constexpr int kThreads = 256;
+// Workgroups of a launch at most.  A launch has fewer than 2^32 work items, 2^24 of these
+// workgroups, which volumes of 2^33 cells (worst case) would exceed; those walk their
+// slices instead.
+constexpr int64_t kMostBlocks = 1 << 23;
 
 // The pixel that owns cell c0, off[p0] <= c0 < off[p0 + 1], of HW pixels: every wave
 // searches by itself, 64 pixels at a time (four rounds for 2^24 of them; a binary search
@@ -657,10 +661,6 @@ struct CensusAllArgs {
 };
 
 constexpr int kCensusChunk = 2 * kThreads;
-// Workgroups of a launch at most.  A launch has fewer than 2^32 work items, 2^24 of these
-// workgroups, which volumes of 2^33 cells (worst case) would exceed; those walk their
-// slices instead.
-constexpr int64_t kCensusBlocks = 1 << 23;
 
 struct CensusLds {
     int rel[kCensusChunk + 1];     // a pixel's first cell, from the slice's first
@@ -750,20 +750,24 @@ __global__ __launch_bounds__(kThreads) void cost_census_kernel(Src src) {
     }
 }
 
-template <int C>
-hipError_t census_walk(Runner& r, std::vector<CensusAllArgs>& args) {
-    auto slices = [](const CensusAllArgs& a) {    // in the worst case
-        return ((int64_t)a.H * a.W * a.N + kCensusChunk - 1) / kCensusChunk;
-    };
+// The workgroups of a launch over slices, args[i].nblk each; true if they were too many
+// and are fewer now, which then walk.
+template <class A>
+bool limit_blocks(std::vector<A>& args, std::vector<uint32_t>& blocks) {
     int64_t all = 0;
-    for (const CensusAllArgs& a : args) all += slices(a);
-    const bool walk = all > kCensusBlocks;
-    const int64_t most = std::max<int64_t>(1, kCensusBlocks / (int64_t)args.size());
-    std::vector<uint32_t> blocks;
-    for (CensusAllArgs& a : args) {
-        a.nblk = (uint32_t)(walk ? std::min(slices(a), most) : slices(a));
+    for (const A& a : args) all += a.nblk;
+    const int64_t most = std::max<int64_t>(1, kMostBlocks / (int64_t)args.size());
+    for (A& a : args) {
+        if (all > kMostBlocks) a.nblk = (uint32_t)std::min<int64_t>(a.nblk, most);
         blocks.push_back(a.nblk);
     }
+    return all > kMostBlocks;
+}
+
+template <int C>
+hipError_t census_walk(Runner& r, std::vector<CensusAllArgs>& args) {
+    std::vector<uint32_t> blocks;
+    const bool walk = limit_blocks(args, blocks);
     return walk ? launch(r, kStCost, cost_census_kernel<Single<CensusAllArgs>, true, C>,
                          cost_census_kernel<Group<CensusAllArgs>, true, C>, args, blocks, kThreads)
                 : launch(r, kStCost, cost_census_kernel<Single<CensusAllArgs>, false, C>,
@@ -788,9 +792,10 @@ hipError_t l2_variant(Runner& r, const std::vector<L2Args>& args,
 }
 
 template <typename T, int C>
-hipError_t l2_walk(Runner& r, const std::vector<L2Args>& args,
-                   const std::vector<uint32_t>& blocks) {
-    return r.tune.cost_stride > 1 ? l2_variant<T, true, C>(r, args, blocks)
+hipError_t l2_walk(Runner& r, std::vector<L2Args>& args) {
+    std::vector<uint32_t> blocks;
+    const bool walk = limit_blocks(args, blocks);
+    return walk || r.tune.cost_stride > 1 ? l2_variant<T, true, C>(r, args, blocks)
                                   : l2_variant<T, false, C>(r, args, blocks);
 }
 
@@ -853,7 +858,6 @@ hipError_t stage_cost_inputs(Runner& r, const Jobs& jobs) {
 hipError_t stage_cost(Runner& r, const Jobs& jobs) {
     std::vector<L2Args> l2[2][2];                  // [u8/f32][gray/colour]
     std::vector<L2Args> full[2][2];
-    std::vector<uint32_t> l2_blocks[2][2];
     std::vector<CensusAllArgs> ca[2];              // [gray/colour]
     const int cpt = r.tune.cost_cpt == 2 || r.tune.cost_cpt == 8 ? r.tune.cost_cpt : 4;
     const int stride = std::max(1, r.tune.cost_stride);
@@ -884,7 +888,6 @@ hipError_t stage_cost(Runner& r, const Jobs& jobs) {
                 continue;
             }
             l2[t][col].push_back(a);
-            l2_blocks[t][col].push_back(a.nblk);
         } else {
             CensusAllArgs a{};
             a.census = j->census_all;
@@ -900,17 +903,18 @@ hipError_t stage_cost(Runner& r, const Jobs& jobs) {
             a.W = j->W;
             a.N = j->N;
             a.cap = (uint32_t)j->cap;
+            a.nblk = (uint32_t)((HW * j->N + kCensusChunk - 1) / kCensusChunk);
             ca[j->C == 3 ? 1 : 0].push_back(a);
         }
     }
     hipError_t e = hipSuccess;
-    if (!l2[0][0].empty() && (e = l2_walk<uint8_t, 1>(r, l2[0][0], l2_blocks[0][0])) != hipSuccess)
+    if (!l2[0][0].empty() && (e = l2_walk<uint8_t, 1>(r, l2[0][0])) != hipSuccess)
         return e;
-    if (!l2[1][0].empty() && (e = l2_walk<float, 1>(r, l2[1][0], l2_blocks[1][0])) != hipSuccess)
+    if (!l2[1][0].empty() && (e = l2_walk<float, 1>(r, l2[1][0])) != hipSuccess)
         return e;
-    if (!l2[0][1].empty() && (e = l2_walk<uint8_t, 3>(r, l2[0][1], l2_blocks[0][1])) != hipSuccess)
+    if (!l2[0][1].empty() && (e = l2_walk<uint8_t, 3>(r, l2[0][1])) != hipSuccess)
         return e;
-    if (!l2[1][1].empty() && (e = l2_walk<float, 3>(r, l2[1][1], l2_blocks[1][1])) != hipSuccess)
+    if (!l2[1][1].empty() && (e = l2_walk<float, 3>(r, l2[1][1])) != hipSuccess)
         return e;
     if (!full[0][0].empty() && (e = l2_full<uint8_t, 1>(r, full[0][0])) != hipSuccess) return e;
     if (!full[1][0].empty() && (e = l2_full<float, 1>(r, full[1][0])) != hipSuccess) return e;
