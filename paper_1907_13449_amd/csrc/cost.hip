@@ -77,6 +77,16 @@ __device__ __forceinline__ int pixel_of(const int64_t* __restrict__ off, int p, 
 template <typename T, int C>
 constexpr int kGroupOf = sizeof(T) == 4 ? 3 : C == 1 ? 3 : 1;
 
+// Items per 100 cells above which a slice takes one cell at a time instead.  An item takes
+// as long as 1.5 cells alone (8-bit), 1.6 (colour), also one of a hull's gap, and where
+// neighbours' windows have little in common a hull is mostly gaps.  9x9x512^2: windows of 7
+// anywhere in 64 hypotheses 379 us in groups, 268 so (8-bit), 429 / 304 (float), 2385 / 1294
+// (colour float); a third of them anywhere in 100, a tenth of the pixels full, 462 / 376,
+// 479 / 365, 2298 / 1801; none anywhere, on the benchmark bounds, 312 / 312 (8-bit), and
+// with 50 for 100 there the same.  Colour 8-bit views have no groups.
+template <typename T, int C>
+constexpr int kSparse = C == 3 ? 50 : 100;
+
 // Views with a replicated edge: padded (y', x') holds the view at (clamp(y' - 1),
 // clamp(x' - L)), y' < H + 2, x' < W + P (one row above and below, L >= G columns left,
 // P - L right).  With it, the two clamped taps of a bilinear row, (clamp(X),
@@ -275,7 +285,8 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
     // case is its own branch-free copy of the loop body.
     // kRoot: the colour norm by root(), whose range the caller looks after: lim[] takes
     // the smallest and largest squared norm other than 0 (as bits, the smallest less 1).
-    auto group = [&](int u, int v, float d, float (&acc)[G], uint32_t (&lim)[2], auto kRoot) {
+    auto group = [&](int u, int v, float d, auto& acc, uint32_t (&lim)[2], auto kRoot) {
+        constexpr int G = std::extent_v<std::remove_reference_t<decltype(acc)>>;
         const Taps<C, G> ref = ld_taps<T, C, G>(
             view_at(th, sh) + ((uint32_t)(v + kPadT) * Wp + u + kPadL) * kElem, plane);
 #pragma unroll
@@ -338,6 +349,26 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
                 view_at(t, 0) + (uint32_t)(clampi(v + (int)y0, -1, H - 1) + kPadT) * row;
             if (t == th) view_row(rt, fy, yes);
             else view_row(rt, fy, no);
+        }
+    };
+
+    // the same with the root where it holds
+    auto sums = [&](int u, int v, float d, auto& acc) {
+        uint32_t lim[2] = {~0u, 0u};
+        if constexpr (C == 1) {
+            group(u, v, d, acc, lim, std::false_type());
+        } else if constexpr (sizeof(T) == 1) {
+            // 8-bit samples: a bilinear sum that is not its reference differs from
+            // it by at least 2^-24, or where that is 0 by a product of two
+            // fractions, each 0 or at least 2^-24 for such shifts
+            if (d == 0.0f || fabsf(d) >= 0x1p-24f)
+                group(u, v, d, acc, lim, std::true_type());
+            else
+                group(u, v, d, acc, lim, std::false_type());
+        } else {
+            group(u, v, d, acc, lim, std::true_type());
+            if (lim[0] < __float_as_uint(kRootMin) - 1u || lim[1] > __float_as_uint(kRootMax))
+                group(u, v, d, acc, lim, std::false_type());
         }
     };
 
@@ -408,6 +439,27 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
         }
         __syncthreads();
         const int ngroups = (int)(total_groups >> 20), nitems = (int)(total_groups & 0xFFFFFu);
+        // one cell at a time: the hulls are mostly gaps
+        if (__builtin_expect(G > 1 && 100 * nitems > kSparse<T, C> * len, 0)) {   // uniform
+            for (int c = threadIdx.x; c < len; c += kThreads) {
+                int i = 0, end = np;              // largest i with rel[i] <= c
+                while (end - i > 1) {
+                    const int mid = (i + end) >> 1;
+                    if (sl.rel[mid] <= c) i = mid; else end = mid;
+                }
+                const int k = sl.lo[i] + c - sl.rel[i];
+                if ((unsigned)k >= (unsigned)N) continue;
+                int u = u0 + i, v = v0;
+                if (u >= W) {
+                    v += u / W;
+                    u %= W;
+                }
+                float acc[1];
+                sums(u, v, a.hyp[k], acc);
+                store(c0 + c, acc[0]);
+            }
+            if constexpr (Walk) continue; else break;
+        }
         for (int j = threadIdx.x; j < nitems; j += kThreads) {
             int x = 0, y = ngroups;               // largest x with pre[x] <= j
             while (y - x > 1) {
@@ -430,24 +482,8 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
                 any |= cell[g] >= 0;
             }
             if (!any) continue;                   // a gap of the hull
-            const float d = a.hyp[k];
             float acc[G];
-            uint32_t lim[2] = {~0u, 0u};
-            if constexpr (C == 1) {
-                group(u, v, d, acc, lim, std::false_type());
-            } else if constexpr (sizeof(T) == 1) {
-                // 8-bit samples: a bilinear sum that is not its reference differs from
-                // it by at least 2^-24, or where that is 0 by a product of two
-                // fractions, each 0 or at least 2^-24 for such shifts
-                if (d == 0.0f || fabsf(d) >= 0x1p-24f)
-                    group(u, v, d, acc, lim, std::true_type());
-                else
-                    group(u, v, d, acc, lim, std::false_type());
-            } else {
-                group(u, v, d, acc, lim, std::true_type());
-                if (lim[0] < __float_as_uint(kRootMin) - 1u || lim[1] > __float_as_uint(kRootMax))
-                    group(u, v, d, acc, lim, std::false_type());
-            }
+            sums(u, v, a.hyp[k], acc);
 #pragma unroll
             for (int g = 0; g < G; ++g)
                 if (cell[g] >= 0) store(c0 + cell[g], acc[g]);
