@@ -389,15 +389,14 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
         for (int i = threadIdx.x; i < npx; i += kThreads)
             if (sl.rel[i] < len && (i + 1 == npx || sl.rel[i + 1] >= len)) atomicMax(&sl.np, i + 1);
         __syncthreads();
-        const int np = sl.np;
+        const int np = sl.np, stop = min(sl.rel[npx], len);     // of the staged pixels' cells
 
         // Groups: a pixel at u = 0 mod G (or the slice's first pixel) with the following
         // pixels of its row up to the next such u that are in the slice.  A group's
         // items are the hypotheses k of the hull of its pixels' slice cells; an item
         // computes the cells (p + g, k) of the group that exist.  The slice cells of pixel
         // i are [max(rel[i], 0), min(rel[i + 1], len)), cell c is hypothesis
-        // lo[i] + c - rel[i]; a pixel whose range is empty -- possible only for bounds
-        // given with hi < lo -- adds nothing.
+        // lo[i] + c - rel[i]; a pixel whose range is empty adds nothing.
         uint32_t cnt[CPT], rec[CPT], uv[CPT], own = 0;
 #pragma unroll
         for (int e = 0; e < CPT; ++e) {
@@ -439,15 +438,24 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
         }
         __syncthreads();
         const int ngroups = (int)(total_groups >> 20), nitems = (int)(total_groups & 0xFFFFFu);
-        // one cell at a time: the hulls are mostly gaps
-        if (__builtin_expect(G > 1 && 100 * nitems > kSparse<T, C> * len, 0)) {   // uniform
-            for (int c = threadIdx.x; c < len; c += kThreads) {
-                int i = 0, end = np;              // largest i with rel[i] <= c
-                while (end - i > 1) {
-                    const int mid = (i + end) >> 1;
-                    if (sl.rel[mid] <= c) i = mid; else end = mid;
+        // One cell at a time: where the hulls are mostly gaps, and where some cells are of
+        // pixels past the staged ones (only if some of those own no cell).
+        const bool gaps = G > 1 && 100 * nitems > kSparse<T, C> * len;
+        if (__builtin_expect(gaps || stop < len, 0)) {    // uniform
+            for (int c = (G > 1 ? 0 : stop) + threadIdx.x; c < len; c += kThreads) {
+                int i = 0, k;
+                if (G > 1 && c < stop) {
+                    int end = np;                 // largest i with rel[i] <= c
+                    while (end - i > 1) {
+                        const int mid = (i + end) >> 1;
+                        if (sl.rel[mid] <= c) i = mid; else end = mid;
+                    }
+                    k = sl.lo[i] + c - sl.rel[i];
+                } else {
+                    const int p = pixel_of(off, p0 + npx, HW, c0 + c);
+                    i = p - p0;
+                    k = lo[p] + (int)(c0 + c - off[p]);
                 }
-                const int k = sl.lo[i] + c - sl.rel[i];
                 if ((unsigned)k >= (unsigned)N) continue;
                 int u = u0 + i, v = v0;
                 if (u >= W) {
@@ -458,7 +466,9 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
                 sums(u, v, a.hyp[k], acc);
                 store(c0 + c, acc[0]);
             }
-            if constexpr (Walk) continue; else break;
+            if constexpr (G > 1) {
+                if constexpr (Walk) continue; else break;
+            }
         }
         for (int j = threadIdx.x; j < nitems; j += kThreads) {
             int x = 0, y = ngroups;               // largest x with pre[x] <= j
