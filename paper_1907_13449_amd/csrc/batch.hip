@@ -21,12 +21,15 @@
 namespace {
 
 constexpr size_t kAlign = 256;
-constexpr size_t kMaxLaunches = 64;       // grouped launches per run (checked)
+// The tables' room: that of 64 launches of every light field with the largest record.  A run
+// can have more launches (a batch of every variant about 80), but a launch's tables hold its
+// own light fields only, and a light field takes part in fewer than 30.
+constexpr size_t kTableLaunches = 64;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 size_t table_bytes(int n) {
-    return kMaxLaunches * (align_up((size_t)n * lf::kMaxArgRecord) + align_up((size_t)(n + 1) * 4));
+    return kTableLaunches * (align_up((size_t)n * lf::kMaxArgRecord) + align_up((size_t)(n + 1) * 4));
 }
 
 lf::Tuning to_tuning(const lf_tuning* t) {
@@ -104,7 +107,7 @@ struct lf_plan : lf::Recorder {
         for (const lf::Job& j : jobs) js.push_back(&j);
         lf_status s = lf::run_depth_jobs(r, js);
         if (s != LF_OK) return s;
-        if (overflow || launches.size() > kMaxLaunches)
+        if (overflow)
             return lf::record_error(LF_EUNSUPPORTED, "%s", "batch plan tables overflow");
         if (!host_tables.empty()) {
             hipError_t e = hipMemcpyAsync(dev_tables, host_tables.data(), host_tables.size(),
