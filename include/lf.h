@@ -324,7 +324,8 @@ typedef struct {
  * per wave in the bounded SGM with 64 lanes per line (their costs run half as
  * many steps ahead); bounded_lanes: 16, 32 or 64 (default) -- lanes per path line
  * of the bounded SGM (the wavefront-to-path schedule): 64 takes one line per wave
- * where the lines are few and four where they are many, 16 and 32 four everywhere;
+ * where the lines are few and four where they are many (between, as the ranges
+ * suit, found on the GPU), 16 and 32 four everywhere;
  * bounded_offsets: 32 (default) or 64 -- the bounded SGM addresses its volumes with
  * 32-bit offsets where their worst-case size is below 2^31 bytes, and with 64-bit
  * addresses and one line per wave otherwise; 64 takes that form everywhere (the

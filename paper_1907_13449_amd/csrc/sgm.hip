@@ -1064,11 +1064,25 @@ struct alignas(16) PixMeta {
     uint32_t q_lo;
     int32_t lohi;
     uint32_t q_hi;
-    int32_t pad;
+    int32_t rows;                            // of pixel 0: not 0 if four lines per wave ran
     __device__ int64_t base(int N) const {   // off - lo
         return (int64_t)(((uint64_t)q_hi << 32) | q_lo) - N;
     }
 };
+
+__device__ __forceinline__ PixMeta pix_meta(int64_t off, int lo, int hi, int N) {
+    // bounds outside the documented 0 <= lo <= hi < N are clamped into it; that
+    // only narrows a range, so its cells stay within the pixel's own
+    lo = clampi(lo, 0, N - 1);
+    hi = clampi(hi, lo, N - 1);
+    PixMeta m;
+    const uint64_t q = (uint64_t)(off - lo + N);
+    m.q_lo = (uint32_t)q;
+    m.lohi = (int32_t)((uint32_t)lo | ((uint32_t)hi << 16));
+    m.q_hi = (uint32_t)(q >> 32);
+    m.rows = 0;
+    return m;
+}
 
 struct MetaArgs {
     gptr<const int64_t> off;
@@ -1085,16 +1099,7 @@ __global__ __launch_bounds__(256) void pix_meta_kernel(Src src) {
         const MetaArgs& a = member(src, vb, b);
         const int p = (int)b * 256 + threadIdx.x;
         if (p >= a.HW) continue;
-        // bounds outside the documented 0 <= lo <= hi < N are clamped into it; that
-        // only narrows a range, so its cells stay within the pixel's own
-        const int lo = clampi(a.lo[p], 0, a.N - 1), hi = clampi(a.hi[p], lo, a.N - 1);
-        PixMeta m;
-        const uint64_t q = (uint64_t)(a.off[p] - lo + a.N);
-        m.q_lo = (uint32_t)q;
-        m.lohi = (int32_t)((uint32_t)lo | ((uint32_t)hi << 16));
-        m.q_hi = (uint32_t)(q >> 32);
-        m.pad = 0;
-        a.meta[p] = m;
+        a.meta[p] = pix_meta(a.off[p], a.lo[p], a.hi[p], a.N);
     }
 }
 
@@ -1107,6 +1112,7 @@ struct BoundedArgs {
     Units units;                   // of the 64-lane kernel (one line per wave)
     int H, W, N;
     uint32_t P1, P2;
+    int chosen;                    // only if the four-line kernel left it (see RowsChoice)
 };
 
 template <int K, int D>
@@ -1277,6 +1283,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void sgm_bounded_paths_kernel(
         const BoundedArgs& a = member(src, vb, b);
         const int u = __builtin_amdgcn_readfirstlane(b * kWavesPerBlock + (threadIdx.x >> 6));
         if (u >= a.units.nunits) continue;            // wave-uniform
+        if (a.chosen && ((const PixMeta*)a.meta)->rows) continue;
         int line[2];
         unit_lines(a.lines, a.units, a.H, a.W, u, line);
         for (int part = 0; part < 2; ++part) {        // one copy of the line loop
@@ -1316,6 +1323,20 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void sgm_bounded_paths_kernel(
 // block's is decoded and its successor's loads are in flight.  Ballots of the
 // decode say which steps have anything but narrow pixels in the middle of a path:
 // one bit test keeps the others to about 18 VALU for four lines.
+
+// Whether the ranges suit this kernel, where the host cannot know.  A step with a wide pixel
+// in any of the four rows takes several times as long as one without, so many of them make
+// it slower than a wave per line, the more so the fewer their cells (figures beside the rule
+// in stage_sgm_final).  Every wave looks at the same 256 sets of four neighbouring pixels,
+// spread over the image, and finds the same: the share of sets with a wide pixel may be up
+// to limit + slope * (cells per pixel), sets whose wide pixels are full ranges counting
+// `full` each.  If it is more, the workgroups write the metadata of the one-line kernel
+// instead, which is launched after this one and finds in it which of the two is to run.
+struct RowsChoice {
+    int on;                        // 0: take four lines
+    float limit, slope, full;
+};
+
 struct RowsArgs {
     gptr<const uint16_t> cost;
     gptr<const int64_t> off;
@@ -1327,6 +1348,9 @@ struct RowsArgs {
     uint32_t P1, P2;
     int npaths;
     int wbase[kMaxPaths + 1];      // direction r owns waves [wbase[r], wbase[r+1])
+    gptr<PixMeta> meta;            // of the one-line kernel
+    uint32_t nblk;                 // workgroups
+    RowsChoice choice;
 };
 
 // What the four rows need of the 16 steps of a block: lane j of a row holds step
@@ -1701,17 +1725,53 @@ __device__ __forceinline__ void bounded_rows_wave(const RowsArgs& a, int wave, u
     }
 }
 
+__device__ __forceinline__ bool rows_suit(const RowsArgs& a) {
+    const int16_t* __restrict__ plo = a.lo;
+    const int16_t* __restrict__ phi = a.hi;
+    const uint32_t HW = (uint32_t)a.H * a.W;
+    int16_t lo[4][4], hi[4][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        // multiples of the golden section: even over the image, whatever its width
+        const uint32_t i = ((threadIdx.x & 63) + 64 * e) * 2654435769u;
+        const uint32_t p = 4 * (uint32_t)(((uint64_t)i * (HW / 4)) >> 32);
+        __builtin_memcpy(lo[e], plo + p, 8);
+        __builtin_memcpy(hi[e], phi + p, 8);
+    }
+    const int64_t cells = min(a.off[HW], (int64_t)a.dir_stride);
+    int part = 0, full = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        bool some = false, all = false;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int l = clampi(lo[e][q], 0, a.N - 1), h = clampi(hi[e][q], l, a.N - 1);
+            const bool wide = h - l >= kRowsNarrow, whole = h - l == a.N - 1;
+            some |= wide && !whole;
+            all |= wide && whole;
+        }
+        part += __popcll(__builtin_amdgcn_ballot_w64(some));
+        full += __popcll(__builtin_amdgcn_ballot_w64(all && !some));
+    }
+    return (float)part + a.choice.full * (float)full <=
+           256.0f * (a.choice.limit + a.choice.slope * ((float)cells / (float)HW));
+}
+
 template <class Src, int NR>
 __global__ __launch_bounds__(64 * kWavesPerBlock, NR <= 4 ? 4 : 2) void sgm_bounded_rows_kernel(Src src) {
     __shared__ __align__(16) uint16_t lds[kWavesPerBlock * 4 * kRowsLds<NR>];
-    for (uint32_t vb = blockIdx.x; vb < src.total; vb += gridDim.x) {
-        uint32_t b;
-        const RowsArgs& a = member(src, vb, b);
-        const int wv = threadIdx.x >> 6;
-        const int w = __builtin_amdgcn_readfirstlane(b * kWavesPerBlock + wv);
-        if (w >= a.wbase[kMaxPaths]) continue;        // wave-uniform
-        bounded_rows_wave<NR>(a, w, lds + wv * 4 * kRowsLds<NR>);
+    uint32_t b;
+    const RowsArgs& a = member(src, blockIdx.x, b);
+    if (a.choice.on && !rows_suit(a)) {               // uniform
+        for (uint32_t p = b * 256 + threadIdx.x; p < (uint32_t)a.H * a.W; p += a.nblk * 256)
+            a.meta[p] = pix_meta(a.off[p], a.lo[p], a.hi[p], a.N);
+        return;
     }
+    if (b == 0 && threadIdx.x == 0) a.meta[0].rows = 1;
+    const int wv = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(b * kWavesPerBlock + wv);
+    if (w >= a.wbase[kMaxPaths]) return;              // wave-uniform
+    bounded_rows_wave<NR>(a, w, lds + wv * 4 * kRowsLds<NR>);
 }
 
 // csum[c] = sum_r Lbuf[r][c] over the cells of the CSR volume; each of a light
@@ -1817,7 +1877,7 @@ hipError_t bounded_variant(Runner& r, const std::vector<BoundedArgs>& args,
 template <int NR>
 hipError_t bounded_rows(Runner& r, const std::vector<RowsArgs>& args) {
     std::vector<uint32_t> blocks;
-    for (const RowsArgs& a : args) blocks.push_back(div_up(a.wbase[kMaxPaths], kWavesPerBlock));
+    for (const RowsArgs& a : args) blocks.push_back(a.nblk);
     return launch(r, kStSgmFinal, sgm_bounded_rows_kernel<Single<RowsArgs>, NR>,
                   sgm_bounded_rows_kernel<Group<RowsArgs>, NR>, args, blocks,
                   64 * kWavesPerBlock);
@@ -1842,6 +1902,53 @@ hipError_t bounded_k(Runner& r, int K, const std::vector<BoundedArgs>& args,
     }
 }
 
+
+// Which bounded SGM kernel: four lines per wave, one, or (both set) the four-line kernel
+// with the choice, and the other after it.
+struct Form {
+    bool rows, one;
+    RowsChoice choice;
+};
+
+// A step of four lines costs the GPU less than half of what four steps of one do, but takes
+// about twice as long as one of those (every pixel of a wave waits for its widest), so it
+// needs lines enough beside the longest one: all path steps over the steps of the longest
+// line (`many`).  Bounded paths in us, one line per wave against four, 12 % full-range
+// pixels: 512x512, N = 100 on the benchmark bounds (4,096) 199 / 219; 640x640 (5,120) 299 /
+// 202; 512x512 with 16 paths (8,192) 382 / 254; 1080x1920, N = 96 (8,640) 1468 / 664.
+// Beyond 128 hypotheses a lane of the one-line form holds three or four: N = 200, 256x256
+// (2,048) 94 / 95, 384x384 (3,072) 190 / 141, 375x450 with 16 paths 458 / 181.
+//
+// With windows of 15 hypotheses and more nearly every step of four lines is a wide one.
+// Call of lf_sgm_aggregate in us, one line against four, windows of 15 everywhere: 640x640,
+// N = 64 229 / 440, N = 96 334 / 562; 900x1000 (7,200) 601 / 645, 743 / 812; 1300x1300
+// (10,400), N = 96 1303 / 1402, 1500x1500 (12,000) 1677 / 1631; 640x640, N = 140 410 / 767,
+// N = 200 482 / 770; 600x640 with 16 paths (9,600), N = 200 871 / 815; 1080x1920, N = 140
+// 1867 / 2364.  Windows of 33: 640x640, N = 64 261 / 460; 1080x1920 1828 / 1538.  Full
+// ranges everywhere: 640x640, N = 16 230 / 344, N = 64 350 / 420, N = 96 602 / 551; 800x800
+// (6,400), N = 16 497 / 432.  So between the sizes where four lines never pay and those
+// where they always do, the ranges decide (RowsChoice; lines fitted to these times and to
+// those of windows of 21, 64 and N and of 7 with a tenth to three quarters of full ranges,
+// at the same sizes: at most 3 % above the better form, 1 to 5 us of them the choice).
+Form bounded_form(const Tuning& tune, int N, bool full_range, uint64_t many) {
+    const int c = (N - 1) / 64;
+    constexpr uint64_t sure[4] = {11000, 11000, 16000, 9000};
+    if (tune.bounded_lanes < 64 || (many > 4500 && N <= kRowsNarrow) || many > sure[c])
+        return {true, false, {}};
+    if (many <= (N > 128 ? 2300 : 4500)) return {false, true, {}};
+    constexpr float limit[3][4] = {{0.30f, 0.34f, 0.37f, 0.54f},
+                                   {0.73f, 0.60f, 0.60f, 0.78f},
+                                   {0.74f, 0.74f, 0.60f, 0.78f}};
+    constexpr float slope[3][4] = {{0.0048f, 0.0080f, 0.0041f, 0.0043f},
+                                   {0.0080f, 0.0105f, 0.0065f, 0.0070f},
+                                   {0.0125f, 0.0125f, 0.0065f, 0.0070f}};
+    const int more = many >= 8500 ? 2 : many >= 6000 ? 1 : 0;
+    RowsChoice ch{1, limit[more][c], slope[more][c],
+                  N > 128 ? 0.45f + 0.0032f * N : 0.6f + 0.005f * N};
+    if (!full_range) return {true, true, ch};
+    const bool rows = ch.full <= ch.limit + ch.slope * N;
+    return {rows, !rows, {}};
+}
 
 }  // namespace
 
@@ -2078,15 +2185,6 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
     std::vector<RowsArgs> rows[3];                 // up to 64, 128, 256 hypotheses
     std::vector<BsumArgs> sums[2][2];              // [16/32-bit sums][8/16 paths]
     std::vector<uint32_t> sum_blocks[2][2];
-    // Four lines per wave, or one.  A step of four lines costs the GPU less than half of
-    // what four steps of one do, but takes about twice as long as one of those (every
-    // pixel of a wave waits for its widest), so it needs lines enough beside the
-    // longest one: all path steps over the steps of the longest line.  Bounded paths
-    // in us, one line per wave against four, 12 % full-range pixels: 512x512, N = 100
-    // on the benchmark bounds (4,096) 199 / 219; 640x640 (5,120) 299 / 202; 512x512
-    // with 16 paths (8,192) 382 / 254; 1080x1920, N = 96 (8,640) 1468 / 664.  Beyond
-    // 128 hypotheses a lane of the one-line form holds three or four: N = 200, 256x256
-    // (2,048) 94 / 95, 384x384 (3,072) 190 / 141, 375x450 with 16 paths 458 / 181.
     // The light fields of a batch with up to 128 hypotheses count, and run, together: a
     // launch takes its longest line's time at least (six light fields, N = 33 .. 96, of
     // 89x197 to 317x414: 336 us by two launches of one line per wave, 411 us by two of
@@ -2108,8 +2206,10 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
         const size_t dir_stride = HW * N;          // worst-case cells per direction
 
         const int big = N > 128;
-        const bool many = r.tune.bounded_lanes < 64 || steps[big] > longest[big] * (big ? 2300 : 4500);
-        if (many && r.tune.bounded_offsets == 32 && dir_stride * 2 + 4 <= (size_t)INT32_MAX) {
+        Form form = bounded_form(r.tune, N, j->full_range, steps[big] / longest[big]);
+        if (r.tune.bounded_offsets != 32 || dir_stride * 2 + 4 > (size_t)INT32_MAX)
+            form.one = true, form.rows = false;
+        if (form.rows) {
             RowsArgs w{};
             w.cost = j->cost;
             w.off = j->offsets;
@@ -2124,10 +2224,15 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
             w.P2 = (uint32_t)sp.P2;
             w.npaths = sp.npaths;
             rows_waves(H, W, sp.npaths, w.wbase);
+            w.meta = pm;
+            w.nblk = div_up(w.wbase[kMaxPaths], kWavesPerBlock);
+            w.choice = form.choice;
             rows[big ? 2 : widest <= 64 ? 0 : 1].push_back(w);
         } else {
             meta.push_back(MetaArgs{j->offsets, j->lo, j->hi, pm, (int)HW, N});
             meta_blocks.push_back(div_up(HW, 256));
+        }
+        if (form.one) {
             BoundedArgs b{};
             b.cost = j->cost;
             b.meta = pm;
@@ -2140,6 +2245,7 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
             b.N = N;
             b.P1 = (uint32_t)sp.P1;
             b.P2 = (uint32_t)sp.P2;
+            b.chosen = form.rows;
             const int K = (N + 63) / 64 - 1;
             paths[K].push_back(b);
             path_blocks[K].push_back(div_up(b.units.nunits, kWavesPerBlock));
@@ -2161,14 +2267,14 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
         (e = launch(r, kStSgmFinal, pix_meta_kernel<Single<MetaArgs>>,
                     pix_meta_kernel<Group<MetaArgs>>, meta, meta_blocks, 256)) != hipSuccess)
         return e;
+    if (!rows[0].empty() && (e = bounded_rows<2>(r, rows[0])) != hipSuccess) return e;
+    if (!rows[1].empty() && (e = bounded_rows<4>(r, rows[1])) != hipSuccess) return e;
+    if (!rows[2].empty() && (e = bounded_rows<8>(r, rows[2])) != hipSuccess) return e;
     for (int K = 0; K < 4; ++K) {
         if (paths[K].empty()) continue;
         e = bounded_k(r, K + 1, paths[K], path_blocks[K]);
         if (e != hipSuccess) return e;
     }
-    if (!rows[0].empty() && (e = bounded_rows<2>(r, rows[0])) != hipSuccess) return e;
-    if (!rows[1].empty() && (e = bounded_rows<4>(r, rows[1])) != hipSuccess) return e;
-    if (!rows[2].empty() && (e = bounded_rows<8>(r, rows[2])) != hipSuccess) return e;
     using BA = BsumArgs;
     if (!sums[0][0].empty() &&
         (e = launch(r, kStSgmFinal, bounded_sum_kernel<Single<BA>, uint16_t, 8>,

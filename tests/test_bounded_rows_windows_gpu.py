@@ -3,7 +3,8 @@ that a pixel's path costs reach the next one through LDS at nearly every step: a
 as single entries over a fill, and as single entries read back.  Against the oracle's
 aggregated cost of Eq. (8)-(9) on identical random costs: bit-exact.
 
-Path steps over the longest line's steps are 8,240, enough for that schedule."""
+Path steps over the longest line's steps are 11,120, enough for that schedule whatever the
+ranges; the workspace says which ran."""
 import numpy as np
 import pytest
 
@@ -24,7 +25,7 @@ def test_alternating_windows(N, widths, period):
     import oracle as lfo
     from paper_1907_13449_amd import lf
     lfo.build(force=False)
-    H, W, npaths, P1, P2 = 520, 515, 16, 17, 700
+    H, W, npaths, P1, P2 = 700, 695, 16, 17, 700
     rng = np.random.default_rng(N)
     v, u = np.mgrid[0:H, 0:W]
     w = np.array(widths)[(u // period + v // period) % len(widths)]
@@ -38,9 +39,11 @@ def test_alternating_windows(N, widths, period):
     cost = rng.integers(0, 3000, size=int(off[-1])).astype(np.uint16)
     print("alternating windows", N, widths, period, flush=True)
     dev = "cuda"
+    ws = lf.workspace(lf.lib.lf_sgm_workspace_size(H, W, N, npaths), dev)
     csum = lf.lf_sgm_aggregate(torch.from_numpy(cost.view(np.int16)).to(dev),
                                torch.from_numpy(off).to(dev), torch.from_numpy(lo).to(dev),
-                               torch.from_numpy(hi).to(dev), N, P1, P2, npaths, 32)
+                               torch.from_numpy(hi).to(dev), N, P1, P2, npaths, 32, ws=ws)
+    assert int(ws[12:16].view(torch.int32)) == 1     # four lines per wave
     dense = np.zeros((H * W, N), dtype=np.int32)
     dense[pix, k] = cost
     ref = lfo.sgm(dense.reshape(H, W, N), P1, P2, npaths, lo=lo, hi=hi).reshape(H * W, N)
