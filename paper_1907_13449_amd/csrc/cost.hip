@@ -98,12 +98,16 @@ constexpr int kSparse = C == 3 ? 50 : 100;
 constexpr int kPadT = 1;
 constexpr int kPadL = 3;
 static_assert(kPadW == 2 * kPadL && kPadH == 2, "the view copy's margins");
-// Columns of the copy.  Single-byte rows of all but small images get 8 more: the bottom
-// taps of 512-column rows 518 bytes apart conflict with the top ones in the cache
-// (376 us of 9x9x512^2, N = 100; 347, 340 and 338 with rows of 522, 524 and 526).  Fits
-// the workspace, which is of floats, and a row of views of 2^31 bytes stays below 2^32.
+// Columns of the copy.  Single-byte rows a multiple of 128 bytes apart, and up to 9 bytes
+// less or more, get up to 23 more: the bottom taps conflict with the top ones in the cache
+// (9x9x256xW, N = 100, in us per pixel column: rows of 498 and 502 bytes 0.38, 506 0.41, 510
+// and 514 0.54, 518 0.40, 522 0.354, 526 0.349, up to 600 0.35; the same around 256, 384,
+// 640, 768, 1024 and 1920).  Fits the workspace, which is of floats, and a row of views of
+// 2^31 bytes stays below 2^32.
 __host__ __device__ __forceinline__ int copy_width(int H, int W, size_t elem) {
-    return W + kPadW + (elem == 1 && H >= 8 && W >= 64 ? 8 : 0);
+    const int w = W + kPadW, m = w & 127;
+    if (elem != 1 || H < 8 || W < 64 || (m > 9 && m < 119)) return w;
+    return (w + 9) / 128 * 128 + 14;
 }
 
 struct PadArgs {
