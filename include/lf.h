@@ -313,9 +313,9 @@ typedef struct {
 } lf_request;
 
 /* Schedule parameters of the kernels; none changes a result.  0 selects the
- * default.  cost_cells_per_thread: 2 (default; one light field by itself takes 4
- * for the boundary-less search, lambda < 0, and where H*W*N is above 2^26), 4 or 8
- * -- cells per thread of one slice of the bounded cost kernel; cost_stride: 1 (default), 2 or 4 --
+ * default.  cost_cells_per_thread: 2, 4 or 8 (default: 2, or 4 where H*W*N of a
+ * light field is above 2^26) -- cells per thread of one slice of the bounded l2 cost
+ * (the boundary-less search, lambda < 0, has no slices); cost_stride: 1 (default), 2 or 4 --
  * slices each cost workgroup walks (persistent workgroups); dense_prefetch: 4, 8
  * or 16 (default) -- path steps of cost loads in flight per wave in the initial
  * SGM with one path line per wave (16-bit path costs, above 128 hypotheses, thin or

@@ -393,15 +393,6 @@ lf::Job depth_job(const lf_view_set* v, const float* hyp, int N, const lf_params
     return j;
 }
 
-// Cells per thread of one light field's bounded cost.  Longer slices spread a slice's
-// setup over more cells but leave fewer workgroups: 4 where every pixel has the full
-// range (1.14 against 1.22 ms, 9x9x512^2, N = 100) or the image is large (377 against
-// 500 us, 1x11x1080x1920 u8, N = 96, 199 M cells at most), 2 otherwise (325 against 357
-// us, 9x9x512^2 f32 with N = 100, 26 M; 21 against 28 us, 5x5x96^2).
-int cost_cells_per_thread(int H, int W, int N, int lambda) {
-    return lambda < 0 || (int64_t)H * W * N > (int64_t)1 << 26 ? 4 : 2;
-}
-
 lf_status run_initial(lf::Runner& r, const lf::Jobs& jobs) {
     {
         prof::Scope _ps(lf::kStCensus, r);
@@ -623,7 +614,7 @@ lf_status lf_cost_volume_bounded(const lf_view_set* views, const float* hyp, int
     j.cap_cells = cap_cells;
     lf::Runner r;
     r.stream = stream;
-    r.tune.cost_cpt = cost_cells_per_thread(H, W, N, 0);   // the bounds are not known here
+    r.tune.cost_cpt = lf::default_cost_cpt({&j});
     LF_CHECK(run_cost(r, {&j}));
     return LF_OK;
 }
@@ -723,7 +714,7 @@ lf_status lf_depth(const lf_view_set* views, const float* hyp, int32_t N, const 
     lf::Job j = depth_job(views, hyp, N, prm, disparity, d_index, ws);
     lf::Runner r;
     r.stream = stream;
-    r.tune.cost_cpt = cost_cells_per_thread(views->H, views->W, N, prm->lambda);
+    r.tune.cost_cpt = lf::default_cost_cpt({&j});
     return run_depth(r, {&j});
 }
 

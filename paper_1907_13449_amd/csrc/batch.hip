@@ -93,6 +93,12 @@ struct lf_plan : lf::Recorder {
         graph = nullptr;
     }
 
+    lf::Jobs jobs_list() const {
+        lf::Jobs js;
+        for (const lf::Job& j : jobs) js.push_back(&j);
+        return js;
+    }
+
     // Records the launches under `t` and enqueues the table upload.
     lf_status record(const lf::Tuning& t, hipStream_t stream) {
         drop_graph();
@@ -103,9 +109,7 @@ struct lf_plan : lf::Recorder {
         lf::Runner r;
         r.rec = this;
         r.tune = t;
-        lf::Jobs js;
-        for (const lf::Job& j : jobs) js.push_back(&j);
-        lf_status s = lf::run_depth_jobs(r, js);
+        lf_status s = lf::run_depth_jobs(r, jobs_list());
         if (s != LF_OK) return s;
         if (overflow)
             return lf::record_error(LF_EUNSUPPORTED, "%s", "batch plan tables overflow");
@@ -192,7 +196,7 @@ lf_status lf_plan_create(const lf_request* reqs, int32_t n, void* ws, size_t ws_
     if (!reqs || n < 1) return lf::record_error(LF_EINVAL, "%s", "empty batch");
     if (!ws || (uintptr_t)ws % kAlign)
         return lf::record_error(LF_EINVAL, "%s", "workspace NULL or not 256-byte aligned");
-    const lf::Tuning t = to_tuning(tuning);
+    lf::Tuning t = to_tuning(tuning);
     if (!valid_tuning(t)) return lf::record_error(LF_EINVAL, "%s", "tuning value out of range");
     for (int i = 0; i < n; ++i) {
         lf_status s = lf::validate_request(&reqs[i], 0, nullptr);
@@ -211,6 +215,8 @@ lf_status lf_plan_create(const lf_request* reqs, int32_t n, void* ws, size_t ws_
     }
     p->dev_tables = at;
     p->table_cap = table_bytes(n);
+    if (!tuning || !tuning->cost_cells_per_thread)
+        t.cost_cpt = lf::default_cost_cpt(p->jobs_list());
     lf_status s = p->record(t, stream);
     if (s != LF_OK) return s;
     *out = p.release();

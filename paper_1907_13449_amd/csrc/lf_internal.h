@@ -268,6 +268,8 @@ hipError_t stage_offsets(Runner& r, const Jobs& jobs);
 // Bounded matching cost (l2 or Census kind) -> cost (and cost_f32).
 hipError_t stage_cost_inputs(Runner& r, const Jobs& jobs);
 hipError_t stage_cost(Runner& r, const Jobs& jobs);
+// The cells per thread of the bounded l2 cost that the default schedule has for these jobs.
+int default_cost_cpt(const Jobs& jobs);
 // Bounded SGM -> csum.
 hipError_t stage_sgm_final(Runner& r, const Jobs& jobs);
 // WTA + sub-pixel (+ median) -> d_index, disparity.
