@@ -313,23 +313,28 @@ typedef struct {
 } lf_request;
 
 /* Schedule parameters of the kernels; none changes a result.  0 selects the
- * default.  cost_cells_per_thread: 2, 4 or 8 (default: 2, or 4 where H*W*N of a
- * light field is above 2^26) -- cells per thread of one slice of the bounded l2 cost
- * (the boundary-less search, lambda < 0, has no slices); cost_stride: 1 (default), 2 or 4 --
- * slices each cost workgroup walks (persistent workgroups); dense_prefetch: 4, 8
- * or 16 (default) -- path steps of cost loads in flight per wave in the initial
- * SGM with one path line per wave (16-bit path costs, above 128 hypotheses, thin or
- * large images), also the steps whose path costs it stages before copying them out;
- * bounded_prefetch: 4 (default), 8 or 16 -- pixel metadata steps in flight
- * per wave in the bounded SGM with 64 lanes per line (their costs run half as
- * many steps ahead); bounded_lanes: 16, 32 or 64 (default) -- lanes per path line
- * of the bounded SGM (the wavefront-to-path schedule): 64 takes one line per wave
- * where the lines are few and four where they are many (between, as the ranges
- * suit, found on the GPU), 16 and 32 four everywhere;
- * bounded_offsets: 32 (default) or 64 -- the bounded SGM addresses its volumes with
- * 32-bit offsets where their worst-case size is below 2^31 bytes, and with 64-bit
- * addresses and one line per wave otherwise; 64 takes that form everywhere (the
- * form of very large volumes, selectable for testing). */
+ * default.
+ *  cost_cells_per_thread: 2, 4 or 8 (default: 2, or 4 where H*W*N of a light field is
+ *    above 2^26) -- cells per thread of one slice of the bounded l2 cost (the
+ *    boundary-less search, lambda < 0, has no slices);
+ *  cost_stride: 1 (default), 2 or 4 -- slices each cost workgroup walks (persistent
+ *    workgroups);
+ *  dense_prefetch: 4, 8 or 16 (default) -- path steps of cost loads in flight per wave
+ *    in the initial SGM with one path line per wave (16-bit path costs, above 128
+ *    hypotheses, thin or large images), also the steps whose path costs it stages
+ *    before copying them out;
+ *  bounded_prefetch: 4 (default), 8 or 16 -- pixel metadata steps in flight per wave in
+ *    the bounded SGM with 64 lanes per line (their costs run half as many steps ahead);
+ *  bounded_lanes: 16, 32 or 64 -- lanes per path line of the bounded SGM (the
+ *    wavefront-to-path schedule): 64 takes one line per wave, 16 and 32 four.  By
+ *    default one where the lines are few, four where they are many, and between as the
+ *    ranges suit, found on the GPU;
+ *  bounded_offsets: 32 (default) or 64 -- the bounded SGM addresses its volumes with
+ *    32-bit offsets where their worst-case size is below 2^31 bytes, and with 64-bit
+ *    addresses and one line per wave otherwise; 64 takes that form everywhere (the
+ *    form of very large volumes, selectable for testing).
+ * lf_plan_tuning gives the values in use: the default ones too, but for bounded_lanes 0
+ * where the light fields do not all take one form or the ranges decide. */
 typedef struct {
     int32_t cost_cells_per_thread;
     int32_t cost_stride;
@@ -368,7 +373,7 @@ lf_status lf_plan_capture(lf_plan* plan);
  * lf_plan_create / lf_plan_autotune (same stream, or synchronised). */
 lf_status lf_plan_run(lf_plan* plan, hipStream_t stream);
 
-/* Kernel launches per run (host), and the tuning in use. */
+/* Kernel launches per run (host), and the tuning in use (see lf_tuning). */
 int32_t lf_plan_launches(const lf_plan* plan);
 lf_status lf_plan_tuning(const lf_plan* plan, lf_tuning* out);
 

@@ -55,7 +55,7 @@ bool valid_tuning(const lf::Tuning& u) {
     };
     return in(u.cost_cpt, {2, 4, 8}) && in(u.cost_stride, {1, 2, 4}) &&
            in(u.dense_depth, {4, 8, 16}) && in(u.bounded_depth, {4, 8, 16}) &&
-           in(u.bounded_lanes, {16, 32, 64}) && in(u.bounded_offsets, {32, 64});
+           in(u.bounded_lanes, {0, 16, 32, 64}) && in(u.bounded_offsets, {32, 64});
 }
 
 }  // namespace
@@ -217,6 +217,7 @@ lf_status lf_plan_create(const lf_request* reqs, int32_t n, void* ws, size_t ws_
     p->table_cap = table_bytes(n);
     if (!tuning || !tuning->cost_cells_per_thread)
         t.cost_cpt = lf::default_cost_cpt(p->jobs_list());
+    if (!t.bounded_lanes) t.bounded_lanes = lf::default_bounded_lanes(p->jobs_list());
     lf_status s = p->record(t, stream);
     if (s != LF_OK) return s;
     *out = p.release();
@@ -238,14 +239,20 @@ lf_status lf_plan_autotune(lf_plan* p, hipStream_t stream, int32_t reps, lf_tuni
         return LF_OK;
     };
     // Phase 1: candidate i takes the i-th value of every list; the stages are
-    // timed separately, so each stage's parameter is chosen on its own.
-    const int cpt[3] = {2, 4, 8}, dd[3] = {4, 8, 16}, bl[3] = {16, 64, 64};
+    // timed separately, so each stage's parameter is chosen on its own.  The third form of
+    // the bounded SGM, by lines and ranges, is timed if it is neither of the others; a
+    // parameter that no light field's kernels have keeps its value.
+    const lf::Jobs js = p->jobs_list();
+    const bool mixed = lf::default_bounded_lanes(js) == 0;
+    const bool slices = lf::uses_cost_slices(js), dense = lf::uses_dense_depth(js);
+    const int cpt[3] = {2, 4, 8}, dd[3] = {4, 8, 16}, bl[3] = {16, 64, 0};
     double best_cost = 1e30, best_dense = 1e30, best_bounded = 1e30;
     lf::Tuning best = p->tune;
     best.cost_stride = 1;
     best.bounded_depth = lf::Tuning{}.bounded_depth;   // the depth phase 1 runs at
     lf_status s = LF_OK;
     for (int i = 0; i < 3 && s == LF_OK; ++i) {
+        if (i == 2 && !slices && !dense && !mixed) break;
         lf::Tuning t;
         t.cost_cpt = cpt[i];
         t.cost_stride = 1;
@@ -253,15 +260,16 @@ lf_status lf_plan_autotune(lf_plan* p, hipStream_t stream, int32_t reps, lf_tuni
         t.bounded_lanes = bl[i];
         double ms[lf::kNumStages];
         if ((s = measure(t, ms)) != LF_OK) break;
-        if (ms[lf::kStCost] < best_cost) best_cost = ms[lf::kStCost], best.cost_cpt = cpt[i];
-        if (ms[lf::kStInitPaths] < best_dense)
+        if (slices && ms[lf::kStCost] < best_cost)
+            best_cost = ms[lf::kStCost], best.cost_cpt = cpt[i];
+        if (dense && ms[lf::kStInitPaths] < best_dense)
             best_dense = ms[lf::kStInitPaths], best.dense_depth = dd[i];
-        if (ms[lf::kStSgmFinal] < best_bounded)
+        if ((bl[i] || mixed) && ms[lf::kStSgmFinal] < best_bounded)
             best_bounded = ms[lf::kStSgmFinal], best.bounded_lanes = bl[i];
     }
     // Phase 2: workgroups walking several cost slices, at the chosen slice size.
     for (int stride : {2, 4}) {
-        if (s != LF_OK) break;
+        if (s != LF_OK || !slices) break;
         lf::Tuning t = best;
         t.cost_stride = stride;
         double ms[lf::kNumStages];
@@ -271,7 +279,7 @@ lf_status lf_plan_autotune(lf_plan* p, hipStream_t stream, int32_t reps, lf_tuni
     // Phase 3: the other prefetch depths of the bounded SGM with one line per wave.
     const int depth0 = best.bounded_depth;
     for (int depth : {4, 8, 16}) {
-        if (s != LF_OK || best.bounded_lanes != 64) break;
+        if (s != LF_OK || best.bounded_lanes == 16) break;
         if (depth == depth0) continue;
         lf::Tuning t = best;
         t.bounded_depth = depth;

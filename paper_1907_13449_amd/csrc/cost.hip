@@ -921,6 +921,10 @@ int default_cost_cpt(const Jobs& jobs) {
     return 2;
 }
 
+bool uses_cost_slices(const Jobs& jobs) {
+    return std::any_of(jobs.begin(), jobs.end(), takes_slices);
+}
+
 hipError_t stage_cost(Runner& r, const Jobs& jobs) {
     std::vector<L2Args> l2[2][2];                  // [u8/f32][gray/colour]
     std::vector<L2Args> full[2][2];

@@ -139,7 +139,8 @@ struct Tuning {
     int cost_stride = 1;     // slices walked per cost workgroup (1, 2, 4)
     int dense_depth = 16;    // steps prefetched by the initial-stage SGM (4, 8, 16)
     int bounded_depth = 4;   // steps prefetched by the bounded SGM, 64 lanes per line (4, 8, 16)
-    int bounded_lanes = 64;  // lanes per path line of the bounded SGM (16, 32, 64)
+    int bounded_lanes = 0;   // lanes per path line of the bounded SGM: 64, 16 or 32 (four
+                             // lines per wave); 0: as the lines and the ranges suit
     int bounded_offsets = 32;  // 32: 32-bit offsets where volumes allow; 64: 64-bit always
 };
 
@@ -268,8 +269,13 @@ hipError_t stage_offsets(Runner& r, const Jobs& jobs);
 // Bounded matching cost (l2 or Census kind) -> cost (and cost_f32).
 hipError_t stage_cost_inputs(Runner& r, const Jobs& jobs);
 hipError_t stage_cost(Runner& r, const Jobs& jobs);
-// The cells per thread of the bounded l2 cost that the default schedule has for these jobs.
+// What the default schedule comes to for these jobs together: the cells per thread of the
+// bounded l2 cost; the lanes per line of the bounded SGM, 0 where not all take the same or
+// the ranges decide.  And whether any of them takes a kernel that a parameter is for.
 int default_cost_cpt(const Jobs& jobs);
+bool uses_cost_slices(const Jobs& jobs);
+int default_bounded_lanes(const Jobs& jobs);
+bool uses_dense_depth(const Jobs& jobs);
 // Bounded SGM -> csum.
 hipError_t stage_sgm_final(Runner& r, const Jobs& jobs);
 // WTA + sub-pixel (+ median) -> d_index, disparity.

@@ -1936,8 +1936,8 @@ struct Form {
 Form bounded_form(const Tuning& tune, int N, bool full_range, uint64_t many) {
     const int c = (N - 1) / 64;
     constexpr uint64_t sure[4] = {11000, 11000, 16000, 9000};
-    if (tune.bounded_lanes < 64 || (many > 4500 && N <= kRowsNarrow) || many > sure[c])
-        return {true, false, {}};
+    if (tune.bounded_lanes) return {tune.bounded_lanes < 64, tune.bounded_lanes == 64, {}};
+    if ((many > 4500 && N <= kRowsNarrow) || many > sure[c]) return {true, false, {}};
     if (many <= (N > 128 ? 2300 : 4500)) return {false, true, {}};
     constexpr float limit[3][4] = {{0.30f, 0.34f, 0.37f, 0.54f},
                                    {0.73f, 0.60f, 0.60f, 0.78f},
@@ -1952,6 +1952,24 @@ Form bounded_form(const Tuning& tune, int N, bool full_range, uint64_t many) {
     const bool rows = ch.full <= ch.limit + ch.slope * N;
     return {rows, !rows, {}};
 }
+
+// The path steps of some light fields.  Those with up to 128 hypotheses count, and run,
+// together: a launch takes its longest line's time at least (six light fields, N = 33 .. 96,
+// of 89x197 to 317x414: 336 us by two launches of one line per wave, 411 us by two of four,
+// 263 us by one of four).
+struct BoundedLines {
+    uint64_t steps[2] = {0, 0}, longest[2] = {1, 1};  // up to 128 hypotheses, more
+    int widest = 0;                                   // of the former
+    explicit BoundedLines(const Jobs& jobs) {
+        for (const Job* j : jobs) {
+            const int big = j->N > 128;
+            steps[big] += (uint64_t)j->H * j->W * j->prm.sgm_final.npaths;
+            longest[big] = std::max(longest[big], (uint64_t)std::max(j->H, j->W));
+            if (!big) widest = std::max(widest, j->N);
+        }
+    }
+    uint64_t many(int N) const { return steps[N > 128] / longest[N > 128]; }
+};
 
 }  // namespace
 
@@ -1981,6 +1999,62 @@ size_t sgm_bounded_scratch_bytes(int H, int W, int N, int npaths) {
     return meta + (size_t)npaths * H * W * N * sizeof(uint16_t);
 }
 
+namespace {
+
+// Four lines per wave, or one (8-bit path costs with the bound of kPad; paths in us, one
+// line against four).  Up to 64 hypotheses four are the faster at every size tried:
+// 4 views of 512x512, N = 40, 272 / 157, of 96x96, N = 32, 24 / 17; 2 of 24x1900,
+// N = 60, 196 / 191, of 1080x1920, N = 64, 1259 / 975.  With more, a step of a line
+// takes longer than in the one-line form, so there have to be lines enough beside the
+// longest one, counted as all path steps over that one's: 53x1674, N = 100 (1,696)
+// 264 / 333; 32x400, 16 paths, N = 128 (2,048) 76 / 77; 128x128, N = 100 (4,096)
+// 35 / 24; 512x512, N = 100, 371 / 295.  And as the lines of all directions are then
+// walked at once, the Census costs have to stay in the 256 MB cache beside the path
+// costs: 256x1024, N = 65 (71 MB) 338 / 291; 2 views of 720x1280, N = 96 (181 MB) 554 /
+// 599, of 1080x1920 (415 MB) 1370 / 1509; 4 of 1080x1080, N = 80 (392 MB) 1545 / 1579.
+struct DenseLines {
+    uint64_t steps = 0, longest = 1;               // of those with more than 64 hypotheses
+    static bool fits(const Job* j) {
+        const int bits = j->C * census_bits(j->prm.census);
+        const int np = std::max(dense_cvol_np(j->N), dense_lnp(j->N, 1));
+        const int64_t HW = (int64_t)j->H * j->W;
+        return j->N <= 128 && bits + j->prm.sgm_init.P2 <= 255 &&
+               bits + 2 * j->prm.sgm_init.P2 <= 255 + j->prm.sgm_init.P1 &&
+               HW * np <= (int64_t)kRowsVolume &&
+               (j->N <= 64 || j->nv * HW * dense_cvol_np(j->N) <= (int64_t)128 << 20);
+    }
+    explicit DenseLines(const Jobs& jobs) {
+        for (const Job* j : jobs)
+            if (j->N > 64 && fits(j)) {
+                steps += (uint64_t)j->nv * j->H * j->W * j->prm.sgm_init.npaths;
+                longest = std::max(longest, (uint64_t)std::max(j->H, j->W));
+            }
+    }
+    bool four(const Job* j) const { return fits(j) && (j->N <= 64 || steps > 2048 * longest); }
+};
+
+}  // namespace
+
+bool uses_dense_depth(const Jobs& jobs) {
+    Jobs bounded;                                  // the others have no initial stage
+    for (const Job* j : jobs)
+        if (j->prm.lambda >= 0) bounded.push_back(j);
+    const DenseLines lines(bounded);
+    return std::any_of(bounded.begin(), bounded.end(),
+                       [&](const Job* j) { return !lines.four(j); });
+}
+
+int default_bounded_lanes(const Jobs& jobs) {
+    const BoundedLines lines(jobs);
+    bool rows = true, one = true;
+    for (const Job* j : jobs) {
+        const Form f = bounded_form(Tuning{}, j->N, j->full_range, lines.many(j->N));
+        rows &= !f.one;
+        one &= !f.rows;
+    }
+    return rows ? 16 : one ? 64 : 0;
+}
+
 hipError_t stage_sgm_initial(Runner& r, const Jobs& jobs, int part) {
     std::vector<CcvArgs> ccv[2];                   // [gray/colour]
     std::vector<uint32_t> ccv_blocks[2];
@@ -1994,31 +2068,7 @@ hipError_t stage_sgm_initial(Runner& r, const Jobs& jobs, int part) {
     std::vector<uint32_t> row_blocks[2];
     std::vector<ExportArgs> ex_cost, ex_sum;       // outputs for checking
     std::vector<uint32_t> ex_cost_blocks, ex_sum_blocks;
-    // Four lines per wave, or one (8-bit path costs with the bound of kPad; paths in us, one
-    // line against four).  Up to 64 hypotheses four are the faster at every size tried:
-    // 4 views of 512x512, N = 40, 272 / 157, of 96x96, N = 32, 24 / 17; 2 of 24x1900,
-    // N = 60, 196 / 191, of 1080x1920, N = 64, 1259 / 975.  With more, a step of a line
-    // takes longer than in the one-line form, so there have to be lines enough beside the
-    // longest one, counted as all path steps over that one's: 53x1674, N = 100 (1,696)
-    // 264 / 333; 32x400, 16 paths, N = 128 (2,048) 76 / 77; 128x128, N = 100 (4,096)
-    // 35 / 24; 512x512, N = 100, 371 / 295.  And as the lines of all directions are then
-    // walked at once, the Census costs have to stay in the 256 MB cache beside the path
-    // costs: 256x1024, N = 65 (71 MB) 338 / 291; 2 views of 720x1280, N = 96 (181 MB) 554 /
-    // 599, of 1080x1920 (415 MB) 1370 / 1509; 4 of 1080x1080, N = 80 (392 MB) 1545 / 1579.
-    auto fits_rows = [](const Job* j) {
-        const int bits = j->C * census_bits(j->prm.census);
-        const int64_t cells = (int64_t)j->H * j->W * std::max(dense_cvol_np(j->N), dense_lnp(j->N, 1));
-        return j->N <= 128 && bits + j->prm.sgm_init.P2 <= 255 &&
-               bits + 2 * j->prm.sgm_init.P2 <= 255 + j->prm.sgm_init.P1 &&
-               cells <= (int64_t)kRowsVolume &&
-               (j->N <= 64 || (int64_t)j->nv * j->H * j->W * dense_cvol_np(j->N) <= (int64_t)128 << 20);
-    };
-    uint64_t steps = 0, longest = 1;               // of those with more than 64 hypotheses
-    for (const Job* j : jobs)
-        if (j->N > 64 && fits_rows(j)) {
-            steps += (uint64_t)j->nv * j->H * j->W * j->prm.sgm_init.npaths;
-            longest = std::max(longest, (uint64_t)std::max(j->H, j->W));
-        }
+    const DenseLines lines(jobs);
     for (const Job* j : jobs) {
         const int H = j->H, W = j->W, N = j->N, NPc = dense_cvol_np(N);
         const size_t HW = (size_t)H * W;
@@ -2065,7 +2115,7 @@ hipError_t stage_sgm_initial(Runner& r, const Jobs& jobs, int part) {
         d.wblocks = div_up(d.units.nunits, kWavesPerBlock);
         const int K = (N + 63) / 64 - 1;
         const int v = lt == 0 && K <= 1 && bits + 2 * sp.P2 <= 255 + sp.P1 ? 2 : lt;
-        if (fits_rows(j) && (N <= 64 || steps > 2048 * longest)) {
+        if (lines.four(j)) {
             DenseRowsArgs w{};
             w.cvol = cvol;
             w.Lbuf = (uint8_t*)Lbuf;
@@ -2188,18 +2238,7 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
     std::vector<RowsArgs> rows[3];                 // up to 64, 128, 256 hypotheses
     std::vector<BsumArgs> sums[2][2];              // [16/32-bit sums][8/16 paths]
     std::vector<uint32_t> sum_blocks[2][2];
-    // The light fields of a batch with up to 128 hypotheses count, and run, together: a
-    // launch takes its longest line's time at least (six light fields, N = 33 .. 96, of
-    // 89x197 to 317x414: 336 us by two launches of one line per wave, 411 us by two of
-    // four, 263 us by one of four).
-    uint64_t steps[2] = {0, 0}, longest[2] = {1, 1};  // up to 128 hypotheses, more
-    int widest = 0;                                // of the former
-    for (const Job* j : jobs) {
-        const int big = j->N > 128;
-        steps[big] += (uint64_t)j->H * j->W * j->prm.sgm_final.npaths;
-        longest[big] = std::max(longest[big], (uint64_t)std::max(j->H, j->W));
-        if (!big) widest = std::max(widest, j->N);
-    }
+    const BoundedLines lines(jobs);
     for (const Job* j : jobs) {
         const int H = j->H, W = j->W, N = j->N;
         const size_t HW = (size_t)H * W;
@@ -2209,7 +2248,7 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
         const size_t dir_stride = HW * N;          // worst-case cells per direction
 
         const int big = N > 128;
-        Form form = bounded_form(r.tune, N, j->full_range, steps[big] / longest[big]);
+        Form form = bounded_form(r.tune, N, j->full_range, lines.many(N));
         if (r.tune.bounded_offsets != 32 || dir_stride * 2 + 4 > (size_t)INT32_MAX)
             form.one = true, form.rows = false;
         if (form.rows) {
@@ -2230,7 +2269,7 @@ hipError_t stage_sgm_final(Runner& r, const Jobs& jobs) {
             w.meta = pm;
             w.nblk = div_up(w.wbase[kMaxPaths], kWavesPerBlock);
             w.choice = form.choice;
-            rows[big ? 2 : widest <= 64 ? 0 : 1].push_back(w);
+            rows[big ? 2 : lines.widest <= 64 ? 0 : 1].push_back(w);
         } else {
             meta.push_back(MetaArgs{j->offsets, j->lo, j->hi, pm, (int)HW, N});
             meta_blocks.push_back(div_up(HW, 256));
