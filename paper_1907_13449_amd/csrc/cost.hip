@@ -81,12 +81,14 @@ constexpr int kGroupOf = sizeof(T) == 4 ? 3 : C == 1 ? 3 : 1;
 // Items per 100 cells above which a slice takes one cell at a time instead.  An item takes
 // as long as 1.5 cells alone (8-bit), 1.6 (colour), also one of a hull's gap, and where
 // neighbours' windows have little in common a hull is mostly gaps.  9x9x512^2: windows of 7
-// anywhere in 64 hypotheses 379 us in groups, 268 so (8-bit), 429 / 304 (float), 2385 / 1294
+// anywhere in 64 hypotheses 379 us in groups, 268 so (8-bit), 429 / 304 (float), 2385 / 1288
 // (colour float); a third of them anywhere in 100, a tenth of the pixels full, 462 / 376,
-// 479 / 365, 2298 / 1801; none anywhere, on the benchmark bounds, 312 / 312 (8-bit), and
-// with 50 for 100 there the same.  Colour 8-bit views have no groups.
+// 479 / 365, 2298 / 1995; a twentieth 317 / 309, 328 / 313, 1481 / 1360; on the benchmark
+// bounds the same.  With 50 for 75 windows anywhere gain more (a third 1745 us), but colour
+// float views of real bounds lose (7x3x61x1867, N = 137, 607 us for 512).  Colour 8-bit
+// views have no groups.
 template <typename T, int C>
-constexpr int kSparse = C == 3 ? 50 : 100;
+constexpr int kSparse = C == 3 ? 75 : 100;
 
 // Views with a replicated edge: padded (y', x') holds the view at (clamp(y' - 1),
 // clamp(x' - L)), y' < H + 2, x' < W + P (one row above and below, L >= G columns left,
@@ -445,9 +447,8 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
         const int ngroups = (int)(total_groups >> 20), nitems = (int)(total_groups & 0xFFFFFu);
         // One cell at a time: where the hulls are mostly gaps, and where some cells are of
         // pixels past the staged ones (only if some of those own no cell).
-        const bool gaps = G > 1 && 100 * nitems > kSparse<T, C> * len;
-        if (__builtin_expect(gaps || stop < len, 0)) {    // uniform
-            for (int c = (G > 1 ? 0 : stop) + threadIdx.x; c < len; c += kThreads) {
+        auto singles = [&](int from) {
+            for (int c = from + threadIdx.x; c < len; c += kThreads) {
                 int i = 0, k;
                 if (G > 1 && c < stop) {
                     int end = np;                 // largest i with rel[i] <= c
@@ -471,11 +472,18 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
                 sums(u, v, a.hyp[k], acc);
                 store(c0 + c, acc[0]);
             }
+        };
+        const bool gaps = G > 1 && 100 * nitems > kSparse<T, C> * len;
+        // before the items, or after them, as the registers come out better: after them the
+        // gray kernels took 4 % longer, before them the colour float one 6 %
+        constexpr bool kAfter = C == 3 && sizeof(T) == 4;
+        if (!kAfter && __builtin_expect(gaps || stop < len, 0)) {    // uniform
+            singles(G > 1 ? 0 : stop);
             if constexpr (G > 1) {
                 if constexpr (Walk) continue; else break;
             }
         }
-        for (int j = threadIdx.x; j < nitems; j += kThreads) {
+        for (int j = threadIdx.x; j < (kAfter && gaps ? 0 : nitems); j += kThreads) {
             int x = 0, y = ngroups;               // largest x with pre[x] <= j
             while (y - x > 1) {
                 const int mid = (x + y) >> 1;
@@ -503,6 +511,7 @@ __device__ __forceinline__ void l2_slices(const L2Args& a, uint32_t b, SliceLds<
             for (int g = 0; g < G; ++g)
                 if (cell[g] >= 0) store(c0 + cell[g], acc[g]);
         }
+        if constexpr (kAfter) singles(gaps ? 0 : stop);
         if constexpr (!Walk) break;               // one slice per workgroup
     }
 }
