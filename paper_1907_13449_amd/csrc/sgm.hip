@@ -751,8 +751,8 @@ __device__ __forceinline__ uint32_t pk_next(uint32_t x, uint32_t y) {
 // k >= N (the bound of kPad: those then never win a min).  Lane j holds the pixel of step
 // j of a block of 16, as byte offsets, and a step reads them by a row broadcast; the
 // next block's costs are in flight.  A row's path costs are written by one instruction
-// (past the caches where the rows are whole lines: 286 us, 4 views of 512x512, N = 100,
-// for 389 through them; 344 us by the one-line form, 1.07 GB written).
+// (past the caches where the rows are whole lines: 281 us, 4 views of 512x512, N = 100, 1.07
+// GB written; a third more through the caches; 313 us by the one-line form).
 struct DenseRowsArgs {
     gptr<const uint8_t> cvol;      // [nv][H*W][NPc]
     gptr<uint8_t> Lbuf;            // [npaths][nv][H*W][NP]
@@ -906,8 +906,12 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void sgm_dense_rows_kernel(Src
     for (uint32_t vb = blockIdx.x; vb < src.total; vb += gridDim.x) {
         uint32_t b;
         const DenseRowsArgs& a = member(src, vb, b);
-        const int z = (int)(b / a.wblocks);                   // the view
-        const uint32_t wb = b - (uint32_t)z * a.wblocks;
+        // The views in turn, so that the directions of the image's longer side, the first
+        // for a wide one, start with the launch in every view: view by view, the last one's
+        // would end it alone (4 views of 156x624, N = 64: 180 us, 79 in turn; 331x449, N =
+        // 77: 185, 173; of the 2 to 4 views of 346 sizes and shapes 1.11 times as fast).
+        const uint32_t wb = b / (uint32_t)a.nv;
+        const int z = (int)(b - wb * (uint32_t)a.nv);
         const int wave = __builtin_amdgcn_readfirstlane(wb * kWavesPerBlock + (threadIdx.x >> 6));
         if (wave >= a.wbase[kMaxPaths]) continue;             // wave-uniform
         dense_rows_wave<NR>(a, z, wave);
@@ -2002,26 +2006,31 @@ size_t sgm_bounded_scratch_bytes(int H, int W, int N, int npaths) {
 namespace {
 
 // Four lines per wave, or one (8-bit path costs with the bound of kPad; paths in us, one
-// line against four).  Up to 64 hypotheses four are the faster at every size tried:
-// 4 views of 512x512, N = 40, 272 / 157, of 96x96, N = 32, 24 / 17; 2 of 24x1900,
-// N = 60, 196 / 191, of 1080x1920, N = 64, 1259 / 975.  With more, a step of a line
-// takes longer than in the one-line form, so there have to be lines enough beside the
-// longest one, counted as all path steps over that one's: 53x1674, N = 100 (1,696)
-// 264 / 333; 32x400, 16 paths, N = 128 (2,048) 76 / 77; 128x128, N = 100 (4,096)
-// 35 / 24; 512x512, N = 100, 371 / 295.  And as the lines of all directions are then
-// walked at once, the Census costs have to stay in the 256 MB cache beside the path
-// costs: 256x1024, N = 65 (71 MB) 338 / 291; 2 views of 720x1280, N = 96 (181 MB) 554 /
-// 599, of 1080x1920 (415 MB) 1370 / 1509; 4 of 1080x1080, N = 80 (392 MB) 1545 / 1579.
+// line against four).  Up to 64 hypotheses four are the faster at nearly every size tried:
+// 4 views of 512x512, N = 40, 256 / 147, of 96x96, N = 32, 24 / 18; 2 of 24x1900, N = 60,
+// 196 / 189, of 1080x1920, N = 64, 1259 / 902 (but 500x2000 with 16 paths 928 / 1092).  With
+// more, a step of a line takes longer than in the one-line form, so there have to be lines
+// enough beside the longest one, counted as all path steps over that one's: 32x400, 16
+// paths, N = 128 (2,048) 76 / 76; 128x128, N = 100 (4,096) 35 / 23; 512x512, N = 100, 313 /
+// 281.  With 2 views and 8 paths the longest lines of a thin image are left alone all the
+// same: 200x600 98 / 96, 200x700 105 / 120, 275x1650 297 / 361.  And as the lines of all
+// directions are walked at once, the Census costs have to stay in the 256 MB cache beside
+// the path costs: 256x1024, N = 65 (71 MB) 312 / 252; 2 views of 600x1000, N = 100 (125 MB)
+// 395 / 375, of 720x1280, N = 96 (181 MB) 554 / 551, of 1080x1920 (415 MB) 1366 / 1451; 4 of
+// 1080x1080, N = 80 (392 MB) 1543 / 1533.
 struct DenseLines {
     uint64_t steps = 0, longest = 1;               // of those with more than 64 hypotheses
     static bool fits(const Job* j) {
         const int bits = j->C * census_bits(j->prm.census);
         const int np = std::max(dense_cvol_np(j->N), dense_lnp(j->N, 1));
         const int64_t HW = (int64_t)j->H * j->W;
+        const bool thin = std::max(j->H, j->W) > 3 * std::min(j->H, j->W) &&
+                          j->nv * j->prm.sgm_init.npaths < 32;
         return j->N <= 128 && bits + j->prm.sgm_init.P2 <= 255 &&
                bits + 2 * j->prm.sgm_init.P2 <= 255 + j->prm.sgm_init.P1 &&
                HW * np <= (int64_t)kRowsVolume &&
-               (j->N <= 64 || j->nv * HW * dense_cvol_np(j->N) <= (int64_t)128 << 20);
+               (j->N <= 64 ||
+                (!thin && j->nv * HW * dense_cvol_np(j->N) <= (int64_t)128 << 20));
     }
     explicit DenseLines(const Jobs& jobs) {
         for (const Job* j : jobs)
