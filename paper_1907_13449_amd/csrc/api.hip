@@ -256,7 +256,8 @@ size_t plan_cost(Carve& c, int S, int T, int C, int H, int W, const lf_params* p
     const bool census = prm && prm->cost_kind == LF_COST_CENSUS;
     q.census_all =
         census ? (uint64_t*)c.take((size_t)S * T * C * HW * sizeof(uint64_t)) : nullptr;
-    // sized for float32 views (uint8 ones use a quarter of it)
+    // sized for float32 views; uint8 ones use about a quarter of it (a third in colour, a
+    // word per pixel)
     q.padded =
         census ? nullptr
                : c.take((size_t)S * T * C * (H + lf::kPadH) * (W + lf::kPadW) * sizeof(float));

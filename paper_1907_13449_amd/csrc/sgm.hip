@@ -1943,7 +1943,7 @@ Form bounded_form(const Tuning& tune, int N, bool full_range, uint64_t many) {
     if (tune.bounded_lanes) return {tune.bounded_lanes < 64, tune.bounded_lanes == 64, {}};
     if ((many > 4500 && N <= kRowsNarrow) || many > sure[c]) return {true, false, {}};
     if (many <= (N > 128 ? 2300 : 4500)) return {false, true, {}};
-    constexpr float limit[3][4] = {{0.30f, 0.34f, 0.37f, 0.54f},
+    constexpr float limit[3][4] = {{0.30f, 0.34f, 0.20f, 0.54f},
                                    {0.73f, 0.60f, 0.60f, 0.78f},
                                    {0.74f, 0.74f, 0.60f, 0.78f}};
     constexpr float slope[3][4] = {{0.0048f, 0.0080f, 0.0041f, 0.0043f},
