@@ -1333,8 +1333,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void sgm_bounded_paths_kernel(
 
 // Whether the ranges suit this kernel, where the host cannot know.  A step with a wide pixel
 // in any of the four rows takes several times as long as one without, so many of them make
-// it slower than a wave per line, the more so the fewer their cells (figures beside the rule
-// in stage_sgm_final).  Every wave looks at the same 256 sets of four neighbouring pixels,
+// it slower than a wave per line, the more so the fewer their cells (figures beside the
+// bounded_form rule).  Every wave looks at the same 256 sets of four neighbouring pixels,
 // spread over the image, and finds the same: the share of sets with a wide pixel may be up
 // to limit + slope * (cells per pixel), sets whose wide pixels are full ranges counting
 // `full` each.  If it is more, the workgroups write the metadata of the one-line kernel
